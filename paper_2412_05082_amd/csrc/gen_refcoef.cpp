@@ -9,6 +9,12 @@
 // -2k..2k) for k = 2..4, printed as hexadecimal floating-point literals so
 // that they are the float64 values computed by the set-up code.
 //
+// Near the boundary the rows of M and L are the periodic rows with the
+// entries of boundary and outside nodes dropped.  Those of B differ further
+// in the first (and last) cell only, by the point term at the boundary
+// (one-sided mean with full weight): db[i - 1][j - 1] = B(i, j) - B^(i, j),
+// i, j = 1..k, in the first cell; the last cell's is its mirror image.
+//
 // Usage: gen_refcoef <output header>
 #include <cmath>
 #include <cstdio>
@@ -51,6 +57,29 @@ int main(int argc, char** argv) {
       }
       std::fprintf(f, "  };\n");
     }
+    // every near-boundary row must be the periodic row plus db
+    std::fprintf(f, "  static constexpr double db[%d][%d] = {\n", k, k);
+    for (int i = 1; i <= 2 * k; ++i) {
+      const int row = rc.row_of_class[2 * rc.left + i % k];
+      if (i <= k) std::fprintf(f, "      {");
+      for (int j = 1; j < lv.n1 - 1; ++j) {
+        const int o = j - i;
+        if (o < -2 * k || o > 2 * k) continue;
+        for (int m = 0; m < 3; ++m) {
+          const double d = (mats[m]->get(i, j) - mats[m]->get(row, row + o)) * scale[m];
+          const double mirror =
+              (mats[m]->get(lv.n1 - 1 - i, lv.n1 - 1 - j) - mats[m]->get(i, j)) * scale[m];
+          const double tol = 1e-10 * std::fabs(mats[m]->get(row, row) * scale[m]);
+          if (!(std::fabs(mirror) <= tol)) return 1;
+          if (m == 2 && i <= k && j <= k)
+            std::fprintf(f, "%s%a", j == 1 ? "" : ", ", d);
+          else if (!(std::fabs(d) <= tol))
+            return 1;
+        }
+      }
+      if (i <= k) std::fprintf(f, "}%s\n", i < k ? "," : "");
+    }
+    std::fprintf(f, "  };\n");
     std::fprintf(f, "};\n");
   }
   std::fprintf(f, "}  // namespace c0ip\n");

@@ -25,14 +25,20 @@
 // Coefficients: with the default penalty the rows of the periodic classes
 // are h-scaled copies of reference rows (h = 1) that are compile-time
 // constants (generated at build time by gen_refcoef.cpp); every term of the
-// 3D operator then carries the same factor 1/h, applied to the output.  On
-// tiles whose x (y) rows are all periodic the x (y) coefficients are these
-// constants; elsewhere the lanes in boundary classes redo their product with
-// their own row from an LDS copy of the reference-scaled table.  The row
-// class of a plane is the same for the whole workgroup: the z rows are read
-// with wave-uniform addresses.  Output nodes on the faces x, y or z = 1 (the last node) are
-// boundary nodes (zero rows of every 1D factor): tiles cover nodes
-// [0, kN), and extra workgroups write those faces as zeros.
+// 3D operator then carries the same factor 1/h, applied to the output.
+// Along x and y every tile uses these constants: boundary nodes are staged
+// as 0, which drops their columns, and the one other difference of the
+// boundary rows, a k x k block of B in the first and in the last cell (the
+// point term at the boundary), is added by the lanes that own those cells.
+// Rows of boundary nodes are masked on the way out.  (Redoing every product
+// of the boundary tiles with per-lane rows from an LDS table took 441 us
+// for 30 % of the tiles of 3D Q3 128^3 in float64, against 337 us for the
+// other 70 %, in a launch of its own because of its registers.)  The z
+// rows come from the level's reference-scaled table with wave-uniform
+// addresses: a plane's row is the same for the whole workgroup.  Output
+// nodes on the faces x, y or z = 1 (the last node) are boundary nodes:
+// tiles cover nodes [0, kN), and extra workgroups write those faces as
+// zeros.
 #include <algorithm>
 #include <type_traits>
 
@@ -84,22 +90,25 @@ __device__ __forceinline__ T band_ref(const T* v, int p) {
   return a;
 }
 
-// Band product of factor OP for the row at cell position p of class cl:
-// the reference row on tiles whose rows are all periodic (UNIFORM);
-// elsewhere the lanes in boundary classes (every lane on meshes without
-// periodic rows) redo it with their own row of the reference-scaled table
-// in LDS.
-template <typename T, int OP, int K, bool UNIFORM>
-__device__ __forceinline__ T band3(const T* __restrict__ sTab, int nclass, int left, int periodic, int cl,
-                                   const T* v, int p) {
-  constexpr int W = 4 * K + 1, H = 2 * K;
-  if constexpr (UNIFORM) {
-    return band_ref<T, OP, K>(v, p);
-  } else {
-    T a = 0;
-    if (periodic) a = band_ref<T, OP, K>(v, p);
-    if (!periodic || cl != 2 * left + p) a = tile::band_dot<T, OP, K>(sTab + (OP * nclass + cl) * W + H, v, p);
-    return a;
+// The boundary block of B (see above): a += the block's product for the
+// nodes of cell c at position p, v[j] = the input at the cell's node j.
+template <typename T, int K>
+__device__ __forceinline__ void add_boundary_b(T (&a)[K], const T* v, int c, int N) {
+  if (c == 0) {  // rows 1..k-1 here, row k with the next cell
+#pragma unroll
+    for (int p = 1; p < K; ++p)
+#pragma unroll
+      for (int j = 1; j <= K; ++j) a[p] += (T)RefCoef<K>::db[p - 1][j - 1] * v[j];
+  }
+  if (c == 1) {
+#pragma unroll
+    for (int j = 1; j <= K; ++j) a[0] += (T)RefCoef<K>::db[K - 1][j - 1] * v[j - K];
+  }
+  if (c == N - 1) {
+#pragma unroll
+    for (int p = 0; p < K; ++p)
+#pragma unroll
+      for (int j = 0; j < K; ++j) a[p] += (T)RefCoef<K>::db[K - 1 - p][K - 1 - j] * v[j];
   }
 }
 
@@ -114,17 +123,16 @@ struct Geo3 {
   static constexpr int NTH = TX * TYC;
   static constexpr int NXG = TXC / CW, NXI = RY * NXG;
   static constexpr int NST = RX * RY, NL = (NST + NTH - 1) / NTH;
-  static constexpr int TABMAX = 3 * (5 * K + 2) * W;  // row classes: at most 5k+2
   static_assert(TXC % CW == 0, "x items must divide the tile");
   static_assert(NTH % 64 == 0 && NTH <= 1024, "whole waves");
 };
 
 // X M_x on all staged rows, X L_x and X B_x on rows [k, RY - k).  Item
-// (row r, group g of CW cells), rows fastest across lanes.
-template <typename T, class G, bool XIN>
+// (row r, group g of CW cells), rows fastest across lanes; cx0 = the tile's
+// first cell.
+template <typename T, class G>
 __device__ __forceinline__ void xpass3(const T* __restrict__ sX, T* __restrict__ sTM, T* __restrict__ sTL,
-                                       T* __restrict__ sTB, const T* __restrict__ sTab, int nclass, int left,
-                                       int right0, int periodic, int x0, int n1) {
+                                       T* __restrict__ sTB, int cx0, int N) {
   constexpr int K = G::K, CW = G::CW, H = G::H;
   constexpr int LO = Band<2, K>::win_lo(0), HI = Band<2, K>::win_hi() + (CW - 1) * K;
   for (int it = threadIdx.x; it < G::NXI; it += G::NTH) {
@@ -132,18 +140,18 @@ __device__ __forceinline__ void xpass3(const T* __restrict__ sX, T* __restrict__
     T in[HI - LO + 1];
 #pragma unroll
     for (int j = LO; j <= HI; ++j) in[j - LO] = sX[r * G::RXP + g * CW * K + j];
-    auto cls = [&](int col, int p) {
-      return XIN ? 2 * left + p : tile::row_class(clampi(x0 + col, 0, n1 - 1), n1, K, left, right0, periodic);
-    };
     auto pass = [&](auto opc, T* __restrict__ out) {
       constexpr int OP = decltype(opc)::value;
 #pragma unroll
-      for (int p = 0; p < K; ++p)
+      for (int w = 0; w < CW; ++w) {
+        const T* v = in + (w * K + H - LO);
+        T a[K];
 #pragma unroll
-        for (int w = 0; w < CW; ++w) {
-          const int col = (g * CW + w) * K + p;
-          out[col] = band3<T, OP, K, XIN>(sTab, nclass, left, periodic, cls(col, p), in + (w * K + p + H - LO), p);
-        }
+        for (int p = 0; p < K; ++p) a[p] = band_ref<T, OP, K>(v + p, p);
+        if constexpr (OP == 2) add_boundary_b<T, K>(a, v, cx0 + g * CW + w, N);
+#pragma unroll
+        for (int p = 0; p < K; ++p) out[(g * CW + w) * K + p] = a[p];
+      }
     };
     pass(std::integral_constant<int, 0>{}, sTM + r * G::TXP);
     if (r >= K && r < G::RY - K) {
@@ -156,18 +164,12 @@ __device__ __forceinline__ void xpass3(const T* __restrict__ sX, T* __restrict__
 // S1, S2, S3 of this thread's k nodes (x column l, y cell cy).  T_B and
 // T_L hold staged rows [k, RY - k) (node y0 + cy k + p + o is their row
 // cy k + p + k + o), T_M all staged rows (row cy k + p + 2k + o).
-template <typename T, class G, bool YIN>
+template <typename T, class G>
 __device__ __forceinline__ void ypass3(const T* __restrict__ sTM, const T* __restrict__ sTL,
                                        const T* __restrict__ sTB, T (&S1)[G::K], T (&S2)[G::K], T (&S3)[G::K],
-                                       const T* __restrict__ sTab, int nclass, int left, int right0, int periodic,
-                                       int y0, int n1) {
+                                       int cy0, int N) {
   constexpr int K = G::K, TX = G::TX;
   const int l = threadIdx.x % TX, cy = threadIdx.x / TX;
-  int cls[K];
-#pragma unroll
-  for (int p = 0; p < K; ++p)
-    cls[p] = YIN ? 2 * left + p
-                 : tile::row_class(clampi(y0 + cy * K + p, 0, n1 - 1), n1, K, left, right0, periodic);
   constexpr int TXP = G::TXP;
   // one window at a time (the scheduling barriers keep the next window's
   // loads from being hoisted over the current one's products)
@@ -176,7 +178,7 @@ __device__ __forceinline__ void ypass3(const T* __restrict__ sTM, const T* __res
 #pragma unroll
     for (int j = 0; j < 3 * K; ++j) t[j] = sTB[(cy * K + j) * TXP + l];
 #pragma unroll
-    for (int p = 0; p < K; ++p) S1[p] = band3<T, 0, K, YIN>(sTab, nclass, left, periodic, cls[p], t + p + K, p);
+    for (int p = 0; p < K; ++p) S1[p] = band_ref<T, 0, K>(t + p + K, p);
   }
   __builtin_amdgcn_sched_barrier(0);
   {
@@ -185,8 +187,8 @@ __device__ __forceinline__ void ypass3(const T* __restrict__ sTM, const T* __res
     for (int j = 0; j < 3 * K; ++j) t[j] = sTL[(cy * K + j) * TXP + l];
 #pragma unroll
     for (int p = 0; p < K; ++p) {
-      S1[p] += T(2) * band3<T, 1, K, YIN>(sTab, nclass, left, periodic, cls[p], t + p + K, p);
-      S3[p] = band3<T, 0, K, YIN>(sTab, nclass, left, periodic, cls[p], t + p + K, p);
+      S1[p] += T(2) * band_ref<T, 1, K>(t + p + K, p);
+      S3[p] = band_ref<T, 0, K>(t + p + K, p);
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -194,13 +196,17 @@ __device__ __forceinline__ void ypass3(const T* __restrict__ sTM, const T* __res
     T t[5 * K];
 #pragma unroll
     for (int j = 0; j < 5 * K; ++j) t[j] = sTM[(cy * K + j) * TXP + l];
+    T sb[K];
 #pragma unroll
     for (int p = 0; p < K; ++p) {
       const T* v = t + p + 2 * K;
-      S2[p] = band3<T, 0, K, YIN>(sTab, nclass, left, periodic, cls[p], v, p);
-      S3[p] = T(2) * (S3[p] + band3<T, 1, K, YIN>(sTab, nclass, left, periodic, cls[p], v, p));
-      S1[p] += band3<T, 2, K, YIN>(sTab, nclass, left, periodic, cls[p], v, p);
+      S2[p] = band_ref<T, 0, K>(v, p);
+      S3[p] = T(2) * (S3[p] + band_ref<T, 1, K>(v, p));
+      sb[p] = band_ref<T, 2, K>(v, p);
     }
+    add_boundary_b<T, K>(sb, t + 2 * K, cy0 + cy, N);
+#pragma unroll
+    for (int p = 0; p < K; ++p) S1[p] += sb[p];
   }
 }
 
@@ -249,26 +255,26 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned off
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, 0, 0);
 }
 
-template <typename Tin, typename T, class G, bool RES, bool XIN, bool YIN>
+template <typename Tin, typename T, class G, bool RES>
 __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T* __restrict__ b, T* __restrict__ y,
-                                             int n1, const T* __restrict__ ref, T hinv, int nclass, int left,
-                                             int right0, int periodic, int x0, int y0, int c0, int c1, T* __restrict__ sX,
-                                             T* __restrict__ sTM, T* __restrict__ sTL, T* __restrict__ sTB,
-                                             const T* __restrict__ sTab) {
+                                             int N, int n1, const T* __restrict__ ref, T hinv, int nclass, int left,
+                                             int right0, int periodic, int cx0, int cy0, int c0, int c1,
+                                             T* __restrict__ sX, T* __restrict__ sTM, T* __restrict__ sTL,
+                                             T* __restrict__ sTB) {
   constexpr int K = G::K, H = G::H, NL = G::NL, NTH = G::NTH;
-  const int NK = n1 - 1;
+  const int NK = n1 - 1, x0 = cx0 * K, y0 = cy0 * K;
   const size_t plane = (size_t)n1 * n1;
   const unsigned pin = (unsigned)(plane * sizeof(Tin)), pout = (unsigned)(plane * sizeof(T));
   const int l = threadIdx.x % G::TX, cy = threadIdx.x / G::TX;
   const int gx = x0 + l;
-  // in-plane byte offsets of this thread's staged elements (kOff: outside the mesh)
+  // in-plane byte offsets of this thread's staged elements (kOff: boundary or outside)
   unsigned soff[NL];
 #pragma unroll
   for (int q = 0; q < NL; ++q) {
     const int e = threadIdx.x + q * NTH;
     const int r = e / G::RX, c = e - r * G::RX;
     const int sy = y0 - H + r, sx = x0 - H + c;
-    soff[q] = (e < G::NST && sy >= 0 && sy < n1 && sx >= 0 && sx < n1) ? (unsigned)(sy * n1 + sx) * sizeof(Tin)
+    soff[q] = (e < G::NST && sy >= 1 && sy < NK && sx >= 1 && sx < NK) ? (unsigned)(sy * n1 + sx) * sizeof(Tin)
                                                                        : kOff;
   }
   // output offsets (nodes of the tile below kN) and right-hand side offsets
@@ -308,40 +314,43 @@ __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T*
   for (int c = c0 - 2; c <= c1 + 1; ++c) {
     const int ce = c - 2;  // the cell written after this cell's first plane
     const bool emit_c = ce >= c0 && ce < c1;
-    if constexpr (RES) {
-      if (emit_c) {
+    auto load_b = [&]() {  // cell ce; plane 0 is boundary: an empty buffer reads 0
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
-          const int gz = ce * K + j;  // plane 0 is boundary: an empty buffer reads 0
-          const __amdgpu_buffer_rsrc_t r = buf(b + (size_t)gz * plane, gz >= 1 ? pout : 0u);
+      for (int j = 0; j < K; ++j) {
+        const int gz = ce * K + j;
+        const __amdgpu_buffer_rsrc_t r = buf(b + (size_t)gz * plane, gz >= 1 && emit_c ? pout : 0u);
 #pragma unroll
-          for (int p = 0; p < K; ++p) bq[j][p] = buf_load<T>(r, boff[p]);
-        }
+        for (int p = 0; p < K; ++p) bq[j][p] = buf_load<T>(r, boff[p]);
       }
-    }
+    };
     static_for<0, K>([&](auto psc) {
       constexpr int ps = decltype(psc)::value;
       if (ps > 0 && c == c1 + 1) return;
       const int zs = c * K + ps;
       if (zs >= zA && zs <= zB) {
         __syncthreads();  // sX holds plane zs; the previous y passes are done
-        xpass3<T, G, XIN>(sX, sTM, sTL, sTB, sTab, nclass, left, right0, periodic, x0, n1);
+        xpass3<T, G>(sX, sTM, sTL, sTB, cx0, N);
         __syncthreads();
         store_plane();  // plane zs + 1 (unused after zB)
         load_plane(zs + 2);
         T S1[K], S2[K], S3[K];
-        ypass3<T, G, YIN>(sTM, sTL, sTB, S1, S2, S3, sTab, nclass, left, right0, periodic, y0, n1);
+        ypass3<T, G>(sTM, sTL, sTB, S1, S2, S3, cy0, N);
         const int clz = tile::row_class(zs, n1, K, left, right0, periodic);
         zscatter<T, K, ps>(acc, S1, S2, S3, ref, clz, nclass);
       }
       if (ps == 0 && emit_c) {
-        // boundary outputs: zero rows give acc = 0, and b reads 0 there
+        if constexpr (RES) {
+          __builtin_amdgcn_sched_barrier(0);  // not before: the windows of the passes need the registers
+          load_b();
+        }
+        // boundary outputs: x = 0 and y = 0 masked; zero columns of the z rows give
+        // acc = 0 on plane 0; b reads 0 there
 #pragma unroll
         for (int j = 0; j < K; ++j) {
           const __amdgpu_buffer_rsrc_t r = buf(y + (size_t)(ce * K + j) * plane, pout);
 #pragma unroll
           for (int p = 0; p < K; ++p) {
-            const T a = hinv * acc[j][p];
+            const T a = boff[p] == kOff ? T(0) : hinv * acc[j][p];
             buf_store<T>(r, yoff[p], RES ? bq[j][p] - a : a);
           }
         }
@@ -356,15 +365,6 @@ __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T*
 #pragma unroll
       for (int p = 0; p < K; ++p) acc[j][p] = T(0);
   }
-}
-
-template <class G>
-__host__ __device__ inline bool tile3_xin(int periodic, int left, int right0, int x0) {
-  return periodic && x0 >= left && x0 + G::TX <= right0;
-}
-template <class G>
-__host__ __device__ inline bool tile3_yin(int periodic, int left, int right0, int y0) {
-  return periodic && y0 >= left && y0 + G::TY <= right0;
 }
 
 // Zeros on the faces x = kN, y = kN, z = kN (boundary nodes that no tile
@@ -388,51 +388,29 @@ inline int face_blocks(int n1) {
   return (int)((3 * (int64_t)n1 * n1 + 16 * NTH - 1) / (16 * NTH));
 }
 
-// RING = false: one workgroup per (interior tile, z chunk), every x and y
-// row periodic, so all band shapes and coefficients are compile-time.
-// RING = true: the tiles of the boundary ring (per-lane row classes), then
-// the workgroups that zero the faces.  Two launches keep the interior
-// kernel's register budget, and so its occupancy, free of the boundary
-// code.
-template <typename Tin, typename T, class G, bool RES, bool RING>
-__global__ __launch_bounds__(G::NTH) void apply3d_kernel(const Tin* __restrict__ x, const T* __restrict__ b,
-                                                         T* __restrict__ y, int N, int n1, const T* __restrict__ ref,
-                                                         T hinv, int nclass, int left, int right0, int periodic,
-                                                         int zcc, tile::TileOrder ord) {
-  int bx, by;
-  if constexpr (RING) {
-    if ((int)blockIdx.x >= ord.nb) {
-      if (blockIdx.y == 0) zero_faces<T, G::NTH>(y, n1, blockIdx.x - ord.nb);
-      return;
-    }
-    tile::tile_of_block(ord, blockIdx.x, bx, by);
-  } else {
-    if (!tile::tile_of_block(ord, ord.nbp + blockIdx.x, bx, by)) return;
+// One workgroup per (tile, z chunk), each XCD walking a contiguous band of
+// them (x fastest, then y: neighbouring tiles share halos in that XCD's L2),
+// then the workgroups that zero the faces.
+// The register bound holds Q3 float64 at 3 waves per SIMD (residual form at
+// 128^3: 592 us at 2 waves, 509 at 3).
+template <typename Tin, typename T, class G, bool RES>
+__global__ __launch_bounds__(G::NTH, G::K == 3 && sizeof(T) == 8 ? 3 : 1) void apply3d_kernel(
+    const Tin* __restrict__ x, const T* __restrict__ b, T* __restrict__ y, int N, int n1, const T* __restrict__ ref,
+    T hinv, int nclass, int left, int right0, int periodic, int tx, int ty, int nz, int zcc) {
+  const int total = tx * ty * nz, L = blockIdx.x;
+  if (L >= total) {
+    zero_faces<T, G::NTH>(y, n1, L - total);
+    return;
   }
+  const int xcd = L & 7, logical = xcd * (total >> 3) + min(xcd, total & 7) + (L >> 3);
+  const int bx = logical % tx, rest = logical / tx, by = rest % ty, bz = rest / ty;
   __shared__ T sX[G::NL * G::NTH + (G::NL * G::NTH / G::RX + 1) * (G::RXP - G::RX)];
   __shared__ T sTM[G::RY * G::TXP];
   __shared__ T sTL[(G::RY - 2 * G::K) * G::TXP];
   __shared__ T sTB[(G::RY - 2 * G::K) * G::TXP];
-  __shared__ T sTab[RING ? G::TABMAX : 1];
-  const int x0 = bx * G::TX, y0 = by * G::TY;
-  const int c0 = blockIdx.y * zcc, c1 = min(c0 + zcc, N);
-#define C0IP_TILE(XI, YI)                                                                                        \
-  apply3d_tile<Tin, T, G, RES, XI, YI>(x, b, y, n1, ref, hinv, nclass, left, right0, periodic, x0, y0, c0, c1, sX, \
-                                       sTM, sTL, sTB, sTab)
-  if constexpr (RING) {
-    for (int e = threadIdx.x; e < 3 * nclass * G::W; e += G::NTH) sTab[e] = ref[e];
-    // (the first barrier of the plane loop orders the table copy)
-    const bool xin = tile3_xin<G>(periodic, left, right0, x0), yin = tile3_yin<G>(periodic, left, right0, y0);
-    if (xin)
-      C0IP_TILE(true, false);
-    else if (yin)
-      C0IP_TILE(false, true);
-    else
-      C0IP_TILE(false, false);
-  } else {
-    C0IP_TILE(true, true);
-  }
-#undef C0IP_TILE
+  const int c0 = bz * zcc, c1 = min(c0 + zcc, N);
+  apply3d_tile<Tin, T, G, RES>(x, b, y, N, n1, ref, hinv, nclass, left, right0, periodic, bx * G::TXC, by * G::TYC,
+                               c0, c1, sX, sTM, sTL, sTB);
 }
 
 // Tile configuration per degree (k <= 4; the register window of the z
@@ -446,29 +424,23 @@ template <typename Tin, typename T, class G>
 hipError_t apply3d_g(int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s) {
   const int n1 = G::K * N + 1;
   const int tx = (N + G::TXC - 1) / G::TXC, ty = (N + G::TYC - 1) / G::TYC;
-  const tile::TileOrder ord =
-      tile::make_order(tx, ty, [&](int bx) { return tile3_xin<G>(c.periodic, c.left, c.right0, bx * G::TX); },
-                       [&](int by) { return tile3_yin<G>(c.periodic, c.left, c.right0, by * G::TY); });
-  // z chunks: enough workgroups for the whole chip, at most 3k + 1 halo
-  // planes recomputed per chunk
+  // z chunks: 1024 workgroups (what the chip holds at 3 waves per SIMD), down
+  // to one cell per chunk: a chunk recomputes 3k + 1 halo planes, but below
+  // 1024 workgroups the march along z sets the time (3D Q3 32^3 float64: 63 us
+  // at 8 cells per chunk, 43 at 4, 33 at 1).  Twice as many for Q3 float64
+  // from 128^3: there the halos come from HBM once the workgroups of a plane
+  // have drifted apart along a long march (128^3: 476 us against 420; 256^3:
+  // 4239 against 3222; float32 and the other degrees are slower by up to 15 %).
+  const int target = G::K == 3 && sizeof(T) == 8 && N >= 128 ? 2048 : 1024;
   int zcc = N;
-  while (zcc > 8 && (int64_t)tx * ty * ((N + zcc - 1) / zcc) < 1024) zcc = (zcc + 1) / 2;
-  // the ring's slower workgroups take shorter z chunks: 16 per column
-  // (measured best for k = 3 at 32^3, 64^3 and 128^3 cells)
-  const int zcr = std::max(2, N / 16);
-  const int nin = tile::order_blocks(ord) - ord.nbp;
-  const dim3 gring(ord.nb + face_blocks<G::NTH>(n1), (N + zcr - 1) / zcr), gin(nin, (N + zcc - 1) / zcc);
-#define C0IP_LAUNCH(RES, RING, GRID, ZC)                                                                         \
-  apply3d_kernel<Tin, T, G, RES, RING><<<GRID, G::NTH, 0, s>>>(x, b, y, N, n1, c.ref, c.hinv, c.nclass, c.left, \
-                                                               c.right0, c.periodic, ZC, ord)
-  if (b) {
-    C0IP_LAUNCH(true, true, gring, zcr);
-    if (nin > 0) C0IP_LAUNCH(true, false, gin, zcc);
-  } else {
-    C0IP_LAUNCH(false, true, gring, zcr);
-    if (nin > 0) C0IP_LAUNCH(false, false, gin, zcc);
-  }
-#undef C0IP_LAUNCH
+  while (zcc > 1 && (int64_t)tx * ty * ((N + zcc - 1) / zcc) < target) zcc = (zcc + 1) / 2;
+  const int nz = (N + zcc - 1) / zcc, grid = tx * ty * nz + face_blocks<G::NTH>(n1);
+  if (b)
+    apply3d_kernel<Tin, T, G, true><<<grid, G::NTH, 0, s>>>(x, b, y, N, n1, c.ref, c.hinv, c.nclass, c.left,
+                                                            c.right0, c.periodic, tx, ty, nz, zcc);
+  else
+    apply3d_kernel<Tin, T, G, false><<<grid, G::NTH, 0, s>>>(x, b, y, N, n1, c.ref, c.hinv, c.nclass, c.left,
+                                                             c.right0, c.periodic, tx, ty, nz, zcc);
   return hipGetLastError();
 }
 
