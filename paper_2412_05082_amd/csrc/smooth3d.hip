@@ -7,16 +7,27 @@
 // chunk of z cells, and walks the vertex layers vz of the chunk.  The
 // patches of a layer are the (TC+1)^2 patches around the tile's vertices;
 // each covers 2k-1 residual planes, of which k-1 are shared with the next
-// layer.  Per residual plane, once: the forward x and y transforms of every
-// patch's n x n block (n = 2k-1), kept in an LDS ring of 2k-1 planes.  Per
-// layer: the z transform, the division by the eigenvalue sums and the
-// inverse z transform along the n planes of each patch (the result of the
-// lower k planes overwrites their ring slots, the upper k-1 go to k-1
-// extra slots), then per plane the inverse y and x transforms in place,
-// and a gather: each owned node sums the (at most 2 x 2) patches of the
-// layer that contain it into a register accumulator of the layer's 2k-1
-// planes.  The k lowest planes are then complete and are written out.
-// All sums run in a fixed order (deterministic).
+// layer.  The sums over overlapping patches commute with the inverse
+// transforms of the other axes, so every 1D transform runs once per plane
+// and not once per (layer, plane):
+//   * k new residual planes are staged in LDS (the next k are already in
+//     flight in registers);
+//   * x: every (plane, row, patch column px) is transformed once, for the
+//     patches of all rows py that share it, into LDS;
+//   * y and z: thread (px, py, mx) owns the x mode mx of one patch column.
+//     It transforms along y in registers, keeps the 2k-1 planes of its
+//     n = 2k-1 y modes in a register window, and per layer transforms along
+//     z, scales by the tabulated reciprocal eigenvalue sums, transforms back
+//     and adds to a second window, the sum over the layers of the output
+//     planes.  The k lowest planes are then complete; they are transformed
+//     back along y into LDS;
+//   * each (plane, row, cell) item sums the (at most 2 x 2) patches that
+//     contain its row and cell, transforms back along x and writes its k
+//     nodes.
+// Nothing but the staged planes and the x-y modes passes through LDS: about
+// 20 accesses per DoF for k = 3 (keeping every patch's block of a layer in
+// LDS and running six passes over it took about 80).  All sums run in a
+// fixed order (deterministic).
 #include <algorithm>
 
 #include "kernels.h"
@@ -32,7 +43,6 @@ constexpr unsigned kOff = 0x80000000u;  // an offset outside every buffer
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 template <typename T>
 __device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned off) {
   if constexpr (sizeof(T) == 8)
@@ -40,23 +50,15 @@ __device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned off) {
   else
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
-template <typename T>
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned off, T v) {
-  if constexpr (sizeof(T) == 8)
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
-  else
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, 0, 0);
-}
-
 template <int K_, int TC_>
 struct SGeo {
   static constexpr int K = K_, TC = TC_, NTH = 256;
-  static constexpr int n = 2 * K - 1, NN = n * n, P = TC + 1, PP = P * P;
-  static constexpr int RS = (TC + 2) * K - 1;    // staged residual plane: RS x RS nodes
-  static constexpr int SLOT = PP * NN;           // one plane of every patch's block
-  static constexpr int NSLOT = 2 * K - 1 + K - 1;  // ring of 2k-1 planes + k-1 extra
-  static constexpr int OWN = TC * K;             // owned nodes per direction
-  static constexpr int NO = (OWN * OWN + NTH - 1) / NTH;  // owned nodes per thread
+  static constexpr int n = 2 * K - 1, NN = n * n, P = TC + 1;
+  static constexpr int RS = (TC + 2) * K - 1, RSP = RS | 1;  // staged residual plane: RS x RS nodes
+  static constexpr int XW = P * n, XP = XW | 1;              // x modes of a row, odd LDS stride
+  static constexpr int OWN = TC * K;                         // owned nodes per direction
+  static constexpr int SZR = K * RS * RSP, SZX = K * RS * XP, SZU = K * P * n * XP;
+  static_assert(P * P * n <= NTH, "one thread per x mode of a patch column");
 };
 
 // One 1D transform of n values: out[c] = sum_a Q[a][c] in[a] (FWD, Q^T) or
@@ -73,204 +75,183 @@ __device__ __forceinline__ void tr1(const T* q, const T (&in)[n], T (&out)[n]) {
   }
 }
 
-// x (AX = 0) or y (AX = 1) transform of every patch block of one slot, in
-// place, or from the staged residual plane into the slot (FROMR).  Items:
-// (patch, line).
-template <typename T, class G, int AX, bool FWD, bool FROMR, bool UNI>
-__device__ __forceinline__ void pass_xy(T* __restrict__ slot, const T* __restrict__ sR, const T (&q0)[G::NN],
-                                        const T* __restrict__ sQ, int cx0, int cy0, int N) {
-  constexpr int n = G::n, K = G::K, P = G::P;
-  for (int it = threadIdx.x; it < G::PP * n; it += G::NTH) {
-    const int qd = it / n, ln = it - qd * n;
-    const int px = qd % P, py = qd / P;
-    const int vx = cx0 + px, vy = cy0 + py;
-    const bool valid = vx >= 1 && vx <= N - 1 && vy >= 1 && vy <= N - 1;
-    T* blk = slot + qd * G::NN;
-    T in[n], out[n];
-    if (FROMR) {
-      // x transform of row ln (local y) of the patch's residual block
-#pragma unroll
-      for (int a = 0; a < n; ++a) in[a] = valid ? sR[(py * K + ln) * G::RS + px * K + a] : T(0);
-    } else {
-#pragma unroll
-      for (int a = 0; a < n; ++a) in[a] = AX == 0 ? blk[ln * n + a] : blk[a * n + ln];
-    }
-    const int var = pvariant(AX == 0 ? vx : vy, N);
-    if (UNI)
-      tr1<T, n, FWD>(q0, in, out);
-    else
-      tr1<T, n, FWD>(sQ + var * G::NN, in, out);
-#pragma unroll
-    for (int a = 0; a < n; ++a) {
-      if (AX == 0)
-        blk[ln * n + a] = out[a];
-      else
-        blk[a * n + ln] = out[a];
-    }
-  }
-}
-
 template <typename T, class G, bool UNI>
 __device__ __forceinline__ void smooth3d_tile(const T* __restrict__ r, const T* __restrict__ xin, T* __restrict__ xout,
                                               int N, const T* __restrict__ Qg, T omega, int cx0, int cy0, int c0,
-                                              int c1, T* __restrict__ sF,
-                                              T* __restrict__ sR, const T* __restrict__ sQ,
-                                              const T* __restrict__ sLam) {
-  constexpr int K = G::K, n = G::n, NN = G::NN, NTH = G::NTH, NO = G::NO, RING = 2 * K - 1;
+                                              int c1, T* __restrict__ sR, T* __restrict__ sX, T* __restrict__ sU,
+                                              const T* __restrict__ sQ, const T* __restrict__ sLam) {
+  constexpr int K = G::K, TC = G::TC, n = G::n, NN = G::NN, P = G::P, NTH = G::NTH, RS = G::RS, RSP = G::RSP,
+                XP = G::XP, OWN = G::OWN;
   const int n1 = K * N + 1, NK = n1 - 1;
   const size_t plane = (size_t)n1 * n1;
   const unsigned pbytes = (unsigned)(plane * sizeof(T));
+  const int tid = threadIdx.x;
   // interior-variant eigenbasis in registers (wave-uniform)
   T q0[NN];
 #pragma unroll
   for (int i = 0; i < NN; ++i) q0[i] = Qg[i];
-  // owned nodes of this thread: in-plane offsets (kOff: none or boundary)
-  unsigned ooff[NO];
-  int ox[NO], oy[NO];
-#pragma unroll
-  for (int t = 0; t < NO; ++t) {
-    const int e = threadIdx.x + t * NTH;
-    ox[t] = e % G::OWN;
-    oy[t] = e / G::OWN;
-    const int gx = cx0 * K + ox[t], gy = cy0 * K + oy[t];
-    const bool own = e < G::OWN * G::OWN && gx < NK && gy < NK;
-    ooff[t] = own ? (unsigned)(gy * n1 + gx) * sizeof(T) : kOff;
-    if (!own) oy[t] = -1;
-  }
   // staged residual plane: node offsets (kOff outside [1, NK-1]^2)
-  constexpr int NR = (G::RS * G::RS + NTH - 1) / NTH;
+  constexpr int NR = (RS * RS + NTH - 1) / NTH;
   unsigned roff[NR];
 #pragma unroll
   for (int t = 0; t < NR; ++t) {
-    const int e = threadIdx.x + t * NTH;
-    const int i = e % G::RS, j = e / G::RS;
+    const int e = tid + t * NTH;
+    const int j = e / RS, i = e - j * RS;
     const int gx = (cx0 - 1) * K + 1 + i, gy = (cy0 - 1) * K + 1 + j;
-    roff[t] = (e < G::RS * G::RS && gx >= 1 && gx <= NK - 1 && gy >= 1 && gy <= NK - 1)
+    roff[t] = (e < RS * RS && gx >= 1 && gx <= NK - 1 && gy >= 1 && gy <= NK - 1)
                   ? (unsigned)(gy * n1 + gx) * sizeof(T)
                   : kOff;
   }
-  T acc[2 * K - 1][NO];
+  // this thread's x mode mx of patch column (px, py)
+  const int py = tid / G::XW, col = tid - py * G::XW, px = col / n, mx = col - px * n;
+  const int vx = cx0 + px, vy = cy0 + py;
+  const bool mine = tid < P * G::XW;
+  const bool valid = mine && vx >= 1 && vx <= N - 1 && vy >= 1 && vy <= N - 1;
+  const T* qy = UNI ? q0 : sQ + (mine ? pvariant(vy, N) : 0) * NN;
+  T win[n][n], acc[n][n], rec[n][n];  // [plane][y mode]; reciprocal sums [y mode][z mode]
 #pragma unroll
-  for (int j = 0; j < 2 * K - 1; ++j)
+  for (int j = 0; j < n; ++j)
 #pragma unroll
-    for (int t = 0; t < NO; ++t) acc[j][t] = T(0);
-  auto emit = [&](int zp, const T (&a)[NO]) {  // plane zp complete: write the owned nodes
-    if (zp < c0 * K || zp >= c1 * K || zp >= NK) return;
-    const __amdgpu_buffer_rsrc_t ri = buf(xin + (size_t)zp * plane, xin ? pbytes : 0u);
-    const __amdgpu_buffer_rsrc_t ro = buf(xout + (size_t)zp * plane, pbytes);
+    for (int m = 0; m < n; ++m) win[j][m] = acc[j][m] = rec[j][m] = T(0);
+  int zrec = -1;  // z variant of rec
+  const int v0 = max(c0, 1), vend = c1 == N ? N : c1;
+  T v[K][NR];
+  auto load = [&](int vz) {  // residual planes vz k .. vz k + k - 1 (0 beyond the interior)
 #pragma unroll
-    for (int t = 0; t < NO; ++t) {
-      const int gx = cx0 * K + ox[t], gy = cy0 * K + oy[t];
-      const bool bnd = zp == 0 || gx == 0 || gy == 0;
-      const T v = buf_load<T>(ri, ooff[t]) + omega * a[t];
-      buf_store<T>(ro, ooff[t], bnd ? T(0) : v);
+    for (int j = 0; j < K; ++j) {
+      const int zp = vz * K + j;
+      const __amdgpu_buffer_rsrc_t rr = buf(r + (size_t)zp * plane, zp >= 1 && zp <= NK - 1 ? pbytes : 0u);
+#pragma unroll
+      for (int t = 0; t < NR; ++t) v[j][t] = buf_load<T>(rr, roff[t]);
     }
   };
-  const int v0 = max(c0, 1), v1 = min(c1, N - 1);
-  if (c0 == 0) {  // plane 0 is boundary
-    T z[NO];
+  load(v0 - 1);
+  for (int vz = v0 - 1; vz <= vend; ++vz) {
 #pragma unroll
-    for (int t = 0; t < NO; ++t) z[t] = T(0);
-    emit(0, z);
-  }
-  int zdone = (v0 - 1) * K;  // residual planes transformed so far: up to zdone
-  for (int vz = v0; vz <= v1; ++vz) {
-    const int zlo = (vz - 1) * K + 1;  // planes zlo .. zlo + n - 1
-    // forward x, y transforms of the new planes
-    for (int zp = max(zdone + 1, zlo); zp <= zlo + n - 1; ++zp) {
-      const __amdgpu_buffer_rsrc_t rr = buf(r + (size_t)zp * plane, pbytes);
-      T v[NR];
-#pragma unroll
-      for (int t = 0; t < NR; ++t) v[t] = buf_load<T>(rr, roff[t]);
+    for (int j = 0; j < K; ++j)
 #pragma unroll
       for (int t = 0; t < NR; ++t) {
-        const int e = threadIdx.x + t * NTH;
-        if (NR * NTH == G::RS * G::RS || e < G::RS * G::RS) sR[e] = v[t];
+        const int e = tid + t * NTH, row = e / RS;
+        if (NR * NTH == RS * RS || e < RS * RS) sR[j * RS * RSP + e + row * (RSP - RS)] = v[j][t];
       }
-      __syncthreads();
-      T* slot = sF + (zp % RING) * G::SLOT;
-      pass_xy<T, G, 0, true, true, UNI>(slot, sR, q0, sQ, cx0, cy0, N);
-      __syncthreads();
-      pass_xy<T, G, 1, true, false, UNI>(slot, sR, q0, sQ, cx0, cy0, N);
-    }
-    zdone = zlo + n - 1;
+    if (vz < vend) load(vz + 1);
     __syncthreads();
-    // z transform, division, inverse z transform: item (patch, y, x)
-    {
+    // x transform of every row of the new planes (rows fastest across lanes)
+    for (int it = tid; it < K * P * RS; it += NTH) {
+      const int jp = it / RS, row = it - jp * RS, j = jp / P, qx = jp - j * P;
+      const T* src = sR + (j * RS + row) * RSP + qx * K;
+      T* dst = sX + (j * RS + row) * XP + qx * n;
+      T in[n], out[n];
+#pragma unroll
+      for (int a = 0; a < n; ++a) in[a] = src[a];
+      if (UNI)
+        tr1<T, n, true>(q0, in, out);
+      else
+        tr1<T, n, true>(sQ + pvariant(cx0 + qx, N) * NN, in, out);
+#pragma unroll
+      for (int a = 0; a < n; ++a) dst[a] = out[a];
+    }
+    __syncthreads();
+    // the window moves up by k planes; the new ones are transformed along y
+#pragma unroll
+    for (int j = 0; j < n; ++j)
+#pragma unroll
+      for (int m = 0; m < n; ++m) {
+        if (j < K - 1) win[j][m] = win[j + K][m];
+        acc[j][m] = j < K - 1 ? acc[j + K][m] : T(0);
+      }
+    if (valid) {
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        T in[n];
+#pragma unroll
+        for (int a = 0; a < n; ++a) in[a] = sX[(j * RS + py * K + a) * XP + col];
+        tr1<T, n, true>(qy, in, win[K - 1 + j]);
+      }
+    }
+    if (vz >= v0 && vz <= N - 1) {
       const int zv = pvariant(vz, N);
       const T* qz = Qg + zv * NN;
-      const T* lz = sLam + zv * n;
-      for (int it = threadIdx.x; it < G::PP * NN; it += NTH) {
-        const int qd = it / NN, e = it - qd * NN, m = e / n, c = e - m * n;
-        const int px = qd % G::P, py = qd / G::P;
-        const T lxy = sLam[pvariant(cx0 + px, N) * n + c] + sLam[pvariant(cy0 + py, N) * n + m];
-        T in[n], w[n];
+      if (zv != zrec) {
+        zrec = zv;
+        if (valid) {
+          const T lx = sLam[pvariant(vx, N) * n + mx];
 #pragma unroll
-        for (int j = 0; j < n; ++j) in[j] = sF[((zlo + j) % RING) * G::SLOT + it];
-        tr1<T, n, true>(qz, in, w);
+          for (int m = 0; m < n; ++m) {
+            const T lxy = lx + sLam[pvariant(vy, N) * n + m];
 #pragma unroll
-        for (int kz = 0; kz < n; ++kz) w[kz] = w[kz] / (lxy + lz[kz]);
-        tr1<T, n, false>(qz, w, in);
-#pragma unroll
-        for (int j = 0; j < n; ++j) {
-          const int s = j < K ? (zlo + j) % RING : RING + j - K;
-          sF[s * G::SLOT + it] = in[j];
-        }
-      }
-    }
-    __syncthreads();
-    // inverse y then x transforms of every plane of the layer
-    for (int j = 0; j < n; ++j) {
-      T* slot = sF + (j < K ? (zlo + j) % RING : RING + j - K) * G::SLOT;
-      pass_xy<T, G, 1, false, false, UNI>(slot, sR, q0, sQ, cx0, cy0, N);
-    }
-    __syncthreads();
-    for (int j = 0; j < n; ++j) {
-      T* slot = sF + (j < K ? (zlo + j) % RING : RING + j - K) * G::SLOT;
-      pass_xy<T, G, 0, false, false, UNI>(slot, sR, q0, sQ, cx0, cy0, N);
-    }
-    __syncthreads();
-    // gather: each owned node sums the patches of the layer containing it
-#pragma unroll
-    for (int t = 0; t < NO; ++t) {
-      if (oy[t] < 0) continue;
-      const int gx = cx0 * K + ox[t], gy = cy0 * K + oy[t];
-      const int mx = gx / K, rx = gx - mx * K, my = gy / K, ry = gy - my * K;
-#pragma unroll
-      for (int j = 0; j < n; ++j) {
-        const T* slot = sF + (j < K ? (zlo + j) % RING : RING + j - K) * G::SLOT;
-        T s = 0;
-#pragma unroll
-        for (int dy = 0; dy < 2; ++dy) {
-          if (dy == 1 && ry == 0) continue;
-          const int vy = my + dy, ay = gy - (vy - 1) * K - 1;
-#pragma unroll
-          for (int dx = 0; dx < 2; ++dx) {
-            if (dx == 1 && rx == 0) continue;
-            const int vx = mx + dx, ax = gx - (vx - 1) * K - 1;
-            s += slot[((vy - cy0) * G::P + (vx - cx0)) * NN + ay * n + ax];
+            for (int c = 0; c < n; ++c) rec[m][c] = T(1) / (lxy + sLam[zv * n + c]);
           }
         }
-        acc[j][t] += s;
+      }
+      if (valid) {
+#pragma unroll
+        for (int m = 0; m < n; ++m) {
+          T in[n], w[n];
+#pragma unroll
+          for (int j = 0; j < n; ++j) in[j] = win[j][m];
+          tr1<T, n, true>(qz, in, w);
+#pragma unroll
+          for (int c = 0; c < n; ++c) w[c] *= rec[m][c];
+          tr1<T, n, false>(qz, w, in);
+#pragma unroll
+          for (int j = 0; j < n; ++j) acc[j][m] += in[j];
+        }
       }
     }
-    // planes zlo .. zlo + k - 1 are complete
+    // planes (vz - 1) k + 1 .. vz k are complete (plane 0 is boundary)
+    if (vz < v0 && c0 > 0) continue;
+    if (mine) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) emit(zlo + j, acc[j]);
+      for (int j = 0; j < K; ++j) {
+        T u[n];
+        tr1<T, n, false>(qy, acc[j], u);
 #pragma unroll
-    for (int j = 0; j < K - 1; ++j)
+        for (int a = 0; a < n; ++a) sU[((j * P + py) * n + a) * XP + col] = u[a];
+      }
+    }
+    __syncthreads();
+    for (int it = tid; it < K * OWN * TC; it += NTH) {
+      const int jr = it / TC, c = it - jr * TC, j = jr / OWN, oy = jr - j * OWN;
+      const int zp = (vz - 1) * K + 1 + j;
+      const int gx = (cx0 + c) * K, gy = cy0 * K + oy;
+      if (zp < c0 * K || zp >= c1 * K || gx >= NK || gy >= NK) continue;
+      const size_t o = (size_t)zp * plane + (size_t)gy * n1 + gx;
+      T xv[K];
 #pragma unroll
-      for (int t = 0; t < NO; ++t) acc[j][t] = acc[j + K][t];
+      for (int p = 0; p < K; ++p) xv[p] = xin ? xin[o + p] : T(0);
+      // patch row my (and my + 1 unless the node is on the vertex line)
+      const int my = oy / K, ry = oy - my * K;
+      const T* ua = sU + ((j * P + my) * n + K - 1 + ry) * XP + c * n;
+      const T* ub = sU + ((j * P + my + 1) * n + ry - 1) * XP + c * n;
+      T wa[n], wb[n];
 #pragma unroll
-    for (int j = K - 1; j < 2 * K - 1; ++j)
+      for (int m = 0; m < n; ++m) {
+        wa[m] = ua[m];
+        wb[m] = ua[n + m];
+      }
+      if (ry > 0) {
 #pragma unroll
-      for (int t = 0; t < NO; ++t) acc[j][t] = T(0);
-    __syncthreads();  // the next layer overwrites the slots
-  }
-  // planes above the last layer's vertex plane that no later layer reaches
-  if (v1 == N - 1 && v1 >= v0) {
+        for (int m = 0; m < n; ++m) {
+          wa[m] += ub[m];
+          wb[m] += ub[n + m];
+        }
+      }
+      const T* qa = UNI ? q0 : sQ + pvariant(cx0 + c, N) * NN;
+      const T* qb = UNI ? q0 : sQ + pvariant(cx0 + c + 1, N) * NN;
 #pragma unroll
-    for (int j = 0; j < K - 1; ++j) emit(v1 * K + 1 + j, acc[j]);
+      for (int p = 0; p < K; ++p) {
+        T a = 0;
+#pragma unroll
+        for (int m = 0; m < n; ++m) a += qa[(K - 1 + p) * n + m] * wa[m];
+        if (p > 0) {
+#pragma unroll
+          for (int m = 0; m < n; ++m) a += qb[(p > 0 ? p - 1 : 0) * n + m] * wb[m];
+        }
+        const bool bnd = zp == 0 || gy == 0 || gx + p == 0;
+        xout[o + p] = bnd ? T(0) : xv[p] + omega * a;
+      }
+    }
   }
 }
 
@@ -290,53 +271,72 @@ __device__ __forceinline__ void zero_faces3(T* __restrict__ y, int n1, int fb) {
   }
 }
 
+// One workgroup per (tile, z chunk), each XCD walking a contiguous band of
+// them (neighbouring tiles share halos in that XCD's L2), then the
+// workgroups that zero the faces.  Bound by vector instructions (Q3 float32:
+// they issue in 78 % of the time).  3D Q3 128^3, this kernel alone: float32
+// 891 -> 400 us with the register windows in place of six passes over every
+// patch's block in LDS, float64 1826 -> 780 us.  The register bound holds Q3
+// float32 at 4 waves per SIMD (3 waves: 8 % slower).
 template <typename T, class G>
-__global__ __launch_bounds__(G::NTH) void smooth3d_kernel(const T* __restrict__ r, const T* __restrict__ xin,
+__global__ __launch_bounds__(G::NTH, G::K == 3 && sizeof(T) == 4 ? 4 : 1) void smooth3d_kernel(const T* __restrict__ r, const T* __restrict__ xin,
                                                           T* __restrict__ xout, int N, const T* __restrict__ Qg,
-                                                          const T* __restrict__ lamg, T omega, int tx, int zcc) {
+                                                          const T* __restrict__ lamg, T omega, int tx, int nz,
+                                                          int zcc) {
   const int n1 = G::K * N + 1;
-  const int nt = tx * tx;
-  if ((int)blockIdx.x >= nt) {
-    if (blockIdx.y == 0) zero_faces3<T, G::NTH>(xout, n1, blockIdx.x - nt);
+  const int total = tx * tx * nz, L = blockIdx.x;
+  if (L >= total) {
+    zero_faces3<T, G::NTH>(xout, n1, L - total);
     return;
   }
-  __shared__ T sF[G::NSLOT * G::SLOT];
-  __shared__ T sR[G::RS * G::RS];
+  __shared__ T sR[G::SZR];
+  __shared__ T sX[G::SZX];
+  __shared__ T sU[G::SZU];
   __shared__ T sQ[4 * G::NN];
   __shared__ T sLam[4 * G::n];
   for (int e = threadIdx.x; e < 4 * G::NN; e += G::NTH) sQ[e] = Qg[e];
   for (int e = threadIdx.x; e < 4 * G::n; e += G::NTH) sLam[e] = lamg[e];
-  __syncthreads();
-  const int bx = blockIdx.x % tx, by = blockIdx.x / tx;
+  // (the first barrier of the layer loop orders these copies)
+  const int xcd = L & 7, logical = xcd * (total >> 3) + min(xcd, total & 7) + (L >> 3);
+  const int bx = logical % tx, rest = logical / tx, by = rest % tx, bz = rest / tx;
   const int cx0 = bx * G::TC, cy0 = by * G::TC;
-  const int c0 = blockIdx.y * zcc, c1 = min(c0 + zcc, N);
+  const int c0 = bz * zcc, c1 = min(c0 + zcc, N);
   // tiles whose patches are all interior in x and y take the basis in
   // scalar registers (when it fits them)
   constexpr bool kUniFits = G::NN * (int)sizeof(T) / 4 <= 50;
   const bool uni = kUniFits && cx0 >= 2 && cx0 + G::TC <= N - 2 && cy0 >= 2 && cy0 + G::TC <= N - 2;
   if constexpr (kUniFits) {
     if (uni) {
-      smooth3d_tile<T, G, true>(r, xin, xout, N, Qg, omega, cx0, cy0, c0, c1, sF, sR, sQ, sLam);
+      smooth3d_tile<T, G, true>(r, xin, xout, N, Qg, omega, cx0, cy0, c0, c1, sR, sX, sU, sQ, sLam);
       return;
     }
   }
-  smooth3d_tile<T, G, false>(r, xin, xout, N, Qg, omega, cx0, cy0, c0, c1, sF, sR, sQ, sLam);
+  smooth3d_tile<T, G, false>(r, xin, xout, N, Qg, omega, cx0, cy0, c0, c1, sR, sX, sU, sQ, sLam);
 }
 
 template <typename T, int K> struct SmoothCfg;
 template <typename T> struct SmoothCfg<T, 2> { using G = SGeo<2, 8>; };
 template <typename T> struct SmoothCfg<T, 3> { using G = SGeo<3, 6>; };
-template <typename T> struct SmoothCfg<T, 4> { using G = SGeo<4, sizeof(T) == 4 ? 4 : 2>; };
+template <typename T> struct SmoothCfg<T, 4> { using G = SGeo<4, 5>; };
 
 template <typename T, class G>
 hipError_t smooth3d_g(int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega, hipStream_t s) {
   const int n1 = G::K * N + 1;
   const int tx = (N + G::TC - 1) / G::TC;
+  // z chunks: about as many workgroups as the chip holds at once by the
+  // kernel's registers and LDS (float32: 8, 4 and 2 per compute unit for
+  // k = 2, 3, 4; float64 half of that): fewer leave it idle, more recompute
+  // the patches shared between chunks (Q3 64^3 float32: 129 us with 512, 121
+  // with 1024, 134 with 2048).  For k = 4 twice as many (Q4 64^3 float64: 990
+  // us with 256, 856 with 512, 903 with 1024).  Small meshes go down to one
+  // cell per chunk: there the march along z sets the time (Q4 16^3 float64:
+  // 54 us at 4 cells, 28 at 1).
+  const int target = (G::K == 2 ? 2048 : 1024) / (sizeof(T) == 4 ? 1 : 2);
   int zcc = N;
-  while (zcc > 4 && (int64_t)tx * tx * ((N + zcc - 1) / zcc) < 2048) zcc = (zcc + 1) / 2;
+  while (zcc > 1 && (int64_t)tx * tx * ((N + zcc - 1) / zcc) < target) zcc = (zcc + 1) / 2;
   const int nface = (int)((3 * (int64_t)n1 * n1 + 16 * G::NTH - 1) / (16 * G::NTH));
-  const dim3 grid(tx * tx + nface, (N + zcc - 1) / zcc);
-  smooth3d_kernel<T, G><<<grid, G::NTH, 0, s>>>(r, xin, xout, N, e.Q, e.lam, omega, tx, zcc);
+  const int nz = (N + zcc - 1) / zcc;
+  smooth3d_kernel<T, G><<<tx * tx * nz + nface, G::NTH, 0, s>>>(r, xin, xout, N, e.Q, e.lam, omega, tx, nz, zcc);
   return hipGetLastError();
 }
 
