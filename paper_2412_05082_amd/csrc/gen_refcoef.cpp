@@ -1,19 +1,22 @@
 // Build step: writes the header of reference 1D coefficients used as
-// compile-time constants by the 3D operator kernel.
+// compile-time constants by the operator kernels.
 //
 // On a uniform mesh with the default penalty gamma = k(k+1) applied as
 // gamma / h, the rows of the periodic classes of the global 1D matrices
 // (Sec. 4: mass M, stiffness L, and B with its point terms) scale exactly
 // with the mesh size: M = h M^, L = L^ / h, B = B^ / h^3.  The header holds
 // M^, L^, B^ of the periodic rows (cell position p = 0..k-1, offsets
-// -2k..2k) for k = 2..4, printed as hexadecimal floating-point literals so
+// -2k..2k) for k = 2..7, printed as hexadecimal floating-point literals so
 // that they are the float64 values computed by the set-up code.
 //
 // Near the boundary the rows of M and L are the periodic rows with the
 // entries of boundary and outside nodes dropped.  Those of B differ further
 // in the first (and last) cell only, by the point term at the boundary
-// (one-sided mean with full weight): db[i - 1][j - 1] = B(i, j) - B^(i, j),
-// i, j = 1..k, in the first cell; the last cell's is its mirror image.
+// (one-sided mean with full weight): bl holds rows 1..k of B on columns
+// 1..3k, and db[i - 1][j - 1] = B(i, j) - B^(i, j), i, j = 1..k; the last
+// cell's are their mirror images.
+//
+// pt is the embedding table of the transfers (set-up's prolongation_table).
 //
 // Usage: gen_refcoef <output header>
 #include <cmath>
@@ -34,7 +37,7 @@ int main(int argc, char** argv) {
                "// periodic classes of M, L, B for gamma = k(k+1), [p][2k + offset].\n"
                "#pragma once\n\nnamespace c0ip {\ntemplate <int K> struct RefCoef;\n");
   const int N = 16;  // any mesh with periodic rows; the rows are scaled back to h = 1
-  for (int k = 2; k <= 4; ++k) {
+  for (int k = 2; k <= 7; ++k) {
     const c0ip::Level1D lv = c0ip::build_level_1d(k, N, k * (k + 1.0));
     const c0ip::RowClasses rc = c0ip::row_classes(lv);
     if (!rc.periodic) return 1;
@@ -79,6 +82,25 @@ int main(int argc, char** argv) {
       }
       if (i <= k) std::fprintf(f, "}%s\n", i < k ? "," : "");
     }
+    std::fprintf(f, "  };\n");
+    std::fprintf(f, "  static constexpr double bl[%d][%d] = {\n", k, 3 * k);
+    for (int i = 1; i <= k; ++i) {
+      std::fprintf(f, "      {");
+      for (int j = 1; j <= 3 * k; ++j)
+        std::fprintf(f, "%s%a", j == 1 ? "" : ", ", j - i <= 2 * k ? lv.B.get(i, j) * scale[2] : 0.0);
+      std::fprintf(f, "}%s\n", i < k ? "," : "");
+    }
+    std::fprintf(f, "  };\n");
+    // embedding table: value of coarse-cell basis a at position p of fine cell 2 cc + s
+    const std::vector<double> pt = c0ip::prolongation_table(k);
+    std::fprintf(f, "  static constexpr double pt[2][%d][%d] = {\n", k, k + 1);
+    for (int s = 0; s < 2; ++s)
+      for (int p = 0; p < k; ++p) {
+        std::fprintf(f, "      %s{", p == 0 ? "{" : "");
+        for (int a = 0; a <= k; ++a)
+          std::fprintf(f, "%s%a", a == 0 ? "" : ", ", pt[(size_t)(s * k + p) * (k + 1) + a]);
+        std::fprintf(f, "}%s\n", p + 1 < k ? "," : s == 0 ? "}," : "}");
+      }
     std::fprintf(f, "  };\n");
     std::fprintf(f, "};\n");
   }

@@ -96,6 +96,10 @@ hipError_t launch_arnoldi_update(int64_t n, int j, const double* V, int64_t ldv,
 template <typename Tin, typename T>
 hipError_t launch_apply2d(int k, int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s,
                           int nsys = 1, int64_t zs = 0, const int* active = nullptr, Tin* xc = nullptr);
+// The same for the default penalty (c.ref set): compile-time coefficients.
+template <typename Tin, typename T>
+hipError_t launch_apply2d_ref(int k, int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s,
+                              int nsys, int64_t zs, const int* active, Tin* xc);
 template <typename T>
 hipError_t launch_patch2d(int k, int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega,
                           hipStream_t s, int nsys = 1, int64_t zs = 0, const int* active = nullptr);
@@ -118,7 +122,7 @@ template <typename T>
 hipError_t launch_mvs2d_colour_exact(int k, int N, int colour, const LevelCoef<T>& c, const T* Aex, const T* b,
                                      const T* r, T* x, T omega, hipStream_t s);
 // One fused smoothing step S(x, b) (residual in LDS; x_out must not alias x).
-// variant: tile-size variant (0 = default; see avs2d_variants).  With ec:
+// variant: tile-size variant (0 = default; below avs2d_variants).  With ec:
 // the step starts from x + P ec instead (ec: coarse vector of the level
 // below, zc apart between systems; ptab: the embedding table).
 template <typename T>
@@ -126,6 +130,22 @@ hipError_t launch_avs2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& 
                         T omega, hipStream_t s, int nsys = 1, int64_t zs = 0, const int* active = nullptr,
                         int variant = 0, const T* ec = nullptr, const T* ptab = nullptr, int64_t zc = 0);
 int avs2d_variants(int k);
+// The same for the default penalty (c.ref set).
+template <typename T>
+hipError_t launch_step2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* x, const T* b, T* xout,
+                         T omega, hipStream_t s, int nsys, int64_t zs, const int* active, int variant, const T* ec,
+                         int64_t zc);
+// x1 = S(0, b) and r = b - A x1 in one launch (default penalty: c.ref set;
+// k <= 5, else hipErrorNotSupported).  It recomputes the solves of a two-cell
+// halo, which pays only where launches and latency dominate: on levels up to
+// pre2d_max_n(k, element size) cells per direction (0: none).  Measured, fused
+// against two launches: Q3 128^2 float32 7.1 against 9.4 us, 256^2 17.4
+// against 12.6; Q4 128^2 float64 14.3 against 15, 64^2 8.1 against 10; Q6 64^2
+// float64 22.4 against 16.5.
+inline int pre2d_max_n(int k, int elem_size) { return k <= 3 ? 128 : k == 4 ? (elem_size == 4 ? 128 : 64) : k == 5 ? 64 : 0; }
+template <typename T>
+hipError_t launch_pre2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b, T* x1, T* r, T omega,
+                        hipStream_t s);
 template <typename T>
 hipError_t launch_restrict2d(int k, int Nc, const T* table, const T* rf, T* bc, hipStream_t s, int nsys = 1,
                              int64_t zf = 0, int64_t zc = 0, const int* active = nullptr);

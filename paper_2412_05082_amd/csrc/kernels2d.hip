@@ -10,7 +10,6 @@
 #include <algorithm>
 
 #include "exact.h"
-#include "fdm.h"
 #include "kernels.h"
 #include "tiles.h"
 
@@ -23,169 +22,6 @@ using tile::xcd_tile;
 
 // ------------------------------------------------------------------ smoother
 
-template <typename T, int K, int TC>
-__global__ __launch_bounds__(kThreads) void patch2d_kernel(const T* __restrict__ r, const T* __restrict__ xin,
-                                                           T* __restrict__ xout, int N, int n1,
-                                                           const T* __restrict__ Qg, const T* __restrict__ lamg,
-                                                           T omega, int64_t zs, const int* __restrict__ active) {
-  constexpr int n = 2 * K - 1, NN = n * n, NP = TC + 1, S = (TC + 2) * K - 1;
-  // small patches (k <= 3): one thread per patch, transforms in registers (for k = 4 this was measured
-  // several times slower than the passes below)
-  constexpr bool REG = NN <= 25;
-  if (active && !active[blockIdx.z]) return;
-  r += blockIdx.z * zs;
-  xout += blockIdx.z * zs;
-  if (xin) xin += blockIdx.z * zs;
-  constexpr int NL = (S * S + kThreads - 1) / kThreads;
-  __shared__ T sR[S * S];
-  __shared__ T sA[NP * NP * NN];
-  __shared__ T sB[REG ? 1 : NP * NP * NN];
-  __shared__ T sQ[4 * NN];
-  __shared__ T sLam[4 * n];
-  __shared__ T sD[NN];
-  int tbx, tby;
-  xcd_tile(tbx, tby);
-  const int cx0 = tbx * TC, cy0 = tby * TC;
-  const int ox = (cx0 - 1) * K + 1, oy = (cy0 - 1) * K + 1;  // global node of region (0,0)
-  {
-    T v[NL];
-#pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      const int rr = e / S, cc = e - rr * S;
-      const int gy = oy + rr, gx = ox + cc;
-      v[q] = (e < S * S && gx >= 1 && gx <= n1 - 2 && gy >= 1 && gy <= n1 - 2) ? r[(size_t)gy * n1 + gx] : T(0);
-    }
-    tile::stage_eig<T, n, kThreads>(Qg, lamg, sQ, sLam, sD);
-#pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      if (e < S * S) sR[e] = v[q];
-    }
-  }
-  __syncthreads();
-  if constexpr (REG) {
-    // every patch of an interior tile has the interior basis (wave-uniform reads)
-    const bool interior = cx0 >= 2 && cx0 + TC <= N - 2 && cy0 >= 2 && cy0 + TC <= N - 2;
-    for (int p = threadIdx.x; p < NP * NP; p += kThreads) {
-      const int pyl = p / NP, pxl = p - pyl * NP;
-      const int vx = cx0 + pxl, vy = cy0 + pyl;
-      if (vx < 1 || vx > N - 1 || vy < 1 || vy > N - 1) continue;
-      const T* src = sR + (pyl * K) * S + pxl * K;
-      if (interior) {
-        fdm::patch_reg<T, n>(src, S, sA + p * NN, [&](int i) { return Qg[i]; }, [&](int i) { return Qg[i]; },
-                             [&](int ap, int c) { return sD[ap * n + c]; });
-      } else {
-        const int tx = variant(vx, N), ty = variant(vy, N);
-        const T* qx = sQ + tx * NN;
-        const T* qy = sQ + ty * NN;
-        const T* lx = sLam + tx * n;
-        const T* ly = sLam + ty * n;
-        fdm::patch_reg<T, n>(src, S, sA + p * NN, [&](int i) { return qx[i]; }, [&](int i) { return qy[i]; },
-                             [&](int ap, int c) { return T(1) / (lx[c] + ly[ap]); });
-      }
-    }
-    __syncthreads();
-  } else {
-  const T* Q = sQ;
-  const T* lam = sLam;
-  // forward along x: t[a][c] = sum_c' Qx[c'][c] r[a][c']
-  for (int it = threadIdx.x; it < NP * NP * n; it += kThreads) {
-    const int p = it / n, a = it - p * n;
-    const int pyl = p / NP, pxl = p - pyl * NP;
-    const int vx = cx0 + pxl, vy = cy0 + pyl;
-    if (vx < 1 || vx > N - 1 || vy < 1 || vy > N - 1) continue;
-    const T* q = Q + variant(vx, N) * NN;
-    T in[n];
-#pragma unroll
-    for (int c = 0; c < n; ++c) in[c] = sR[(pyl * K + a) * S + pxl * K + c];
-#pragma unroll
-    for (int c = 0; c < n; ++c) {
-      T s = 0;
-#pragma unroll
-      for (int cp = 0; cp < n; ++cp) s += q[cp * n + c] * in[cp];
-      sA[p * NN + a * n + c] = s;
-    }
-  }
-  __syncthreads();
-  // along y: forward with Qy^T, divide by lambda_x + lambda_y, back with Qy
-  for (int it = threadIdx.x; it < NP * NP * n; it += kThreads) {
-    const int p = it / n, c = it - p * n;
-    const int pyl = p / NP, pxl = p - pyl * NP;
-    const int vx = cx0 + pxl, vy = cy0 + pyl;
-    if (vx < 1 || vx > N - 1 || vy < 1 || vy > N - 1) continue;
-    const int ty = variant(vy, N), tx = variant(vx, N);
-    const T* q = Q + ty * NN;
-    const T lx = lam[tx * n + c];
-    T col[n], t[n];
-#pragma unroll
-    for (int a = 0; a < n; ++a) col[a] = sA[p * NN + a * n + c];
-#pragma unroll
-    for (int ap = 0; ap < n; ++ap) {
-      T s = 0;
-#pragma unroll
-      for (int a = 0; a < n; ++a) s += q[a * n + ap] * col[a];
-      t[ap] = s / (lx + lam[ty * n + ap]);
-    }
-#pragma unroll
-    for (int a = 0; a < n; ++a) {
-      T s = 0;
-#pragma unroll
-      for (int ap = 0; ap < n; ++ap) s += q[a * n + ap] * t[ap];
-      sB[p * NN + a * n + c] = s;
-    }
-  }
-  __syncthreads();
-  // back along x: u[a][c'] = sum_c Qx[c'][c] t[a][c]
-  for (int it = threadIdx.x; it < NP * NP * n; it += kThreads) {
-    const int p = it / n, a = it - p * n;
-    const int pyl = p / NP, pxl = p - pyl * NP;
-    const int vx = cx0 + pxl, vy = cy0 + pyl;
-    if (vx < 1 || vx > N - 1 || vy < 1 || vy > N - 1) continue;
-    const T* q = Q + variant(vx, N) * NN;
-    T in[n];
-#pragma unroll
-    for (int c = 0; c < n; ++c) in[c] = sB[p * NN + a * n + c];
-#pragma unroll
-    for (int cp = 0; cp < n; ++cp) {
-      T s = 0;
-#pragma unroll
-      for (int c = 0; c < n; ++c) s += q[cp * n + c] * in[c];
-      sA[p * NN + a * n + cp] = s;
-    }
-  }
-  __syncthreads();
-  }
-  // owned DoFs: sum the covering patches' corrections
-  constexpr int OW = TC * K + 1;
-  const int gx0 = cx0 * K, gy0 = cy0 * K;
-  const int gx1 = (cx0 + TC >= N) ? n1 : (cx0 + TC) * K;
-  const int gy1 = (cy0 + TC >= N) ? n1 : (cy0 + TC) * K;
-  for (int e = threadIdx.x; e < OW * OW; e += kThreads) {
-    const int jj = e / OW, ii = e - jj * OW;
-    const int gx = gx0 + ii, gy = gy0 + jj;
-    if (gx >= gx1 || gy >= gy1) continue;
-    const size_t idx = (size_t)gy * n1 + gx;
-    if (gx == 0 || gx == n1 - 1 || gy == 0 || gy == n1 - 1) {
-      xout[idx] = T(0);
-      continue;
-    }
-    const int vxa = gx / K, vxb = (gx % K == 0) ? vxa : vxa + 1;
-    const int vya = gy / K, vyb = (gy % K == 0) ? vya : vya + 1;
-    T acc = 0;
-    for (int vy = vya; vy <= vyb; ++vy) {
-      if (vy < 1 || vy > N - 1) continue;
-      for (int vx = vxa; vx <= vxb; ++vx) {
-        if (vx < 1 || vx > N - 1) continue;
-        const int p = (vy - cy0) * NP + (vx - cx0);
-        const int c = gx - ((vx - 1) * K + 1), a = gy - ((vy - 1) * K + 1);
-        acc += sA[p * NN + a * n + c];
-      }
-    }
-    xout[idx] = (xin ? xin[idx] : T(0)) + omega * acc;
-  }
-}
-
 template <int K> struct PatchTile2D;
 template <> struct PatchTile2D<2> { static constexpr int TC = 15; };  // 256 patches: one per thread
 template <> struct PatchTile2D<3> { static constexpr int TC = 15; };
@@ -193,17 +29,6 @@ template <> struct PatchTile2D<4> { static constexpr int TC = 8; };
 template <> struct PatchTile2D<5> { static constexpr int TC = 4; };
 template <> struct PatchTile2D<6> { static constexpr int TC = 4; };
 template <> struct PatchTile2D<7> { static constexpr int TC = 4; };
-
-template <typename T, int K>
-hipError_t patch2d_k(int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega, hipStream_t s,
-                     int nsys, int64_t zs, const int* active) {
-  constexpr int TC = PatchTile2D<K>::TC;
-  const int n1 = K * N + 1;
-  const int nt = (N + TC - 1) / TC;
-  dim3 grid(nt, nt, nsys);
-  patch2d_kernel<T, K, TC><<<grid, kThreads, 0, s>>>(r, xin, xout, N, n1, e.Q, e.lam, omega, zs, active);
-  return hipGetLastError();
-}
 
 // Owner-computes smoother step with exact local solves: as patch2d_kernel,
 // but each patch correction is the dense product A_v^{-1} r_v (one inverse
@@ -856,14 +681,6 @@ hipError_t prolong2d_k(int Nc, const T* tab, const T* ec, const T* xin, T* xf, h
 }  // namespace
 
 template <typename T>
-hipError_t launch_patch2d(int k, int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega,
-                          hipStream_t s, int nsys, int64_t zs, const int* active) {
-#define CALL(K) patch2d_k<T, K>(N, e, r, xin, xout, omega, s, nsys, zs, active)
-  C0IP_DISPATCH_K(k, CALL)
-#undef CALL
-}
-
-template <typename T>
 hipError_t launch_patch2d_atomic(int k, int N, const LevelEig<T>& e, const T* r, T* xout, T omega, hipStream_t s) {
 #define CALL(K) patch2d_atomic_k<T, K>(N, e, r, xout, omega, s)
   C0IP_DISPATCH_K(k, CALL)
@@ -934,9 +751,5 @@ template hipError_t launch_mvs2d_colour_exact<double>(int, int, int, const Level
                                                       const double*, const double*, double*, double, hipStream_t);
 template hipError_t launch_mvs2d_colour_exact<float>(int, int, int, const LevelCoef<float>&, const float*,
                                                       const float*, const float*, float*, float, hipStream_t);
-template hipError_t launch_patch2d<double>(int, int, const LevelEig<double>&, const double*, const double*,
-                                           double*, double, hipStream_t, int, int64_t, const int*);
-template hipError_t launch_patch2d<float>(int, int, const LevelEig<float>&, const float*, const float*, float*,
-                                          float, hipStream_t, int, int64_t, const int*);
 
 }  // namespace c0ip

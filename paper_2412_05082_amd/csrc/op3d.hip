@@ -27,9 +27,9 @@
 // constants (generated at build time by gen_refcoef.cpp); every term of the
 // 3D operator then carries the same factor 1/h, applied to the output.
 // Along x and y every tile uses these constants: boundary nodes are staged
-// as 0, which drops their columns, and the one other difference of the
-// boundary rows, a k x k block of B in the first and in the last cell (the
-// point term at the boundary), is added by the lanes that own those cells.
+// as 0, which drops their columns, and the only other boundary rows, the k
+// rows of B next to either end (the point term at the boundary), are
+// corrected by the lanes that own those cells, from constants too.
 // Rows of boundary nodes are masked on the way out.  (Redoing every product
 // of the boundary tiles with per-lane rows from an LDS table took 441 us
 // for 30 % of the tiles of 3D Q3 128^3 in float64, against 337 us for the
@@ -43,14 +43,14 @@
 #include <type_traits>
 
 #include "kernels.h"
-#include "refcoef.h"
+#include "refband.h"
 #include "tiles.h"
 
 namespace c0ip {
 namespace {
 
+using ref::band_ref;
 using tile::Band;
-using tile::clampi;
 
 // The coefficient loads of a boundary plane are loop invariant; hoisted
 // out of the plane loop they would not fit the scalar registers.  Passing
@@ -69,31 +69,15 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Reference row of factor OP (0 = M, 1 = L, 2 = B) at cell position p.
-template <int K, int OP>
-__device__ __forceinline__ constexpr double ref_coef(int p, int j) {
-  if constexpr (OP == 0)
-    return RefCoef<K>::m[p][j];
-  else if constexpr (OP == 1)
-    return RefCoef<K>::l[p][j];
-  else
-    return RefCoef<K>::b[p][j];
-}
-
-// Band product with the reference row (constants) of the periodic class at
-// cell position p; v centred on the row.
-template <typename T, int OP, int K>
-__device__ __forceinline__ T band_ref(const T* v, int p) {
-  T a = 0;
-#pragma unroll
-  for (int o = Band<OP, K>::lo(p); o <= Band<OP, K>::hi(p); ++o) a += (T)ref_coef<K, OP>(p, 2 * K + o) * v[o];
-  return a;
-}
-
-// The boundary block of B (see above): a += the block's product for the
-// nodes of cell c at position p, v[j] = the input at the cell's node j.
+// The boundary rows of B in a cheaper form than ref::boundary_b: a += the
+// difference of their coefficients from the periodic rows times the input, on the k nodes of the boundary cell.  The
+// whole rows reach three cells, for which the window along z leaves no
+// registers (Q3 128^3 float64 spills: 679 us against 418).  The difference
+// rounds at the size of the larger coefficient; for k <= 4 that does not show
+// in the results (at k = 5 it does).
 template <typename T, int K>
 __device__ __forceinline__ void add_boundary_b(T (&a)[K], const T* v, int c, int N) {
+  static_assert(K <= 4, "rounding");
   if (c == 0) {  // rows 1..k-1 here, row k with the next cell
 #pragma unroll
     for (int p = 1; p < K; ++p)

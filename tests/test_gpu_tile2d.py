@@ -1,0 +1,77 @@
+"""The 2D operator and additive smoother on both sides of their switches
+between small and large tiles, and on meshes that cut the tiles (one patch, a
+mesh smaller than a tile, remainders), against the Kronecker form with dense
+1D factors of the library (pinned to the exact ones in test_lib_host.py) and
+SciPy's local eigenbases.  Boundary entries of the inputs hold large values:
+they must not count."""
+import functools
+
+import numpy as np
+import pytest
+import scipy.linalg
+import torch
+
+import paper_2412_05082_amd as P
+from gpu_util import check, dev, fp32_tol, fp64_tol, host, rel_l2
+
+pytestmark = pytest.mark.gpu
+OMEGA = 0.25
+
+
+@functools.lru_cache(maxsize=None)
+def _factors(k, N):
+    M, L, B = P.host_matrices_1d(k, N)
+    n1, n = k * N + 1, 2 * k - 1
+    E, lam = np.zeros(((N - 1) * n, n1)), np.zeros((N - 1) * n)
+    for v in range(1, N):
+        s, r = slice((v - 1) * k + 1, (v - 1) * k + 1 + n), slice((v - 1) * n, v * n)
+        lam[r], Q = scipy.linalg.eigh(B[s, s], M[s, s])
+        E[r, s] = Q.T
+    return M, L, B, E, lam
+
+
+def _apply(k, N, X):
+    M, L, B, _, _ = _factors(k, N)
+    return M @ X @ B + 2.0 * (L @ X @ L) + B @ X @ M
+
+
+def _solves(k, N, R):
+    _, _, _, E, lam = _factors(k, N)
+    return E.T @ ((E @ R @ E.T) / (lam[:, None] + lam[None, :])) @ E
+
+
+LARGE = {2: 256, 3: 256, 4: 256, 5: 128, 6: 128, 7: 128}
+
+
+@pytest.mark.parametrize("k,N", [(k, N) for k in range(2, 8) for N in (2, 4, 16, LARGE[k])])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_operator_and_smoother_2d_tiles(k, N, dtype):
+    n1 = k * N + 1
+    rng = np.random.default_rng(10 * k + N)
+    inner, full = [], []
+    for _ in range(2):
+        v = rng.uniform(-1.0, 1.0, (n1, n1))
+        if dtype == torch.float32:
+            v = v.astype(np.float32).astype(np.float64)
+        z = np.zeros_like(v)
+        z[1:-1, 1:-1] = v[1:-1, 1:-1]
+        inner.append(z)
+        full.append(np.where(z == 0.0, 1e6 * v, v))
+    (x, b), (xf, bf) = inner, full
+    f64 = dtype == torch.float64
+    bar = fp64_tol(2, k, min(N, 8)) if f64 else fp32_tol(2, k, min(N, 8))
+    p = P.Problem(2, N, k, omega=OMEGA)
+    y = torch.full((n1 * n1,), 7.0, dtype=dtype, device="cuda")
+    p.apply_A(dev(xf.ravel(), dtype), y)
+    check(f"A x Q{k} {N}^2 {dtype}", rel_l2(host(y), _apply(k, N, x).ravel()), 1e-12 if f64 else 1e-5)
+    y.fill_(7.0)
+    p.smoother_step(dev(bf.ravel(), dtype), None, y)
+    check(f"S(0,b) Q{k} {N}^2 {dtype}", rel_l2(host(y), OMEGA * _solves(k, N, b).ravel()), bar)
+    ref = (x + OMEGA * _solves(k, N, b - _apply(k, N, x))).ravel()
+    for variant in range(3 if k <= 3 else 2):
+        p.set_variant(variant, dtype=P.C0IP_F64 if f64 else P.C0IP_F32)
+        y.fill_(7.0)
+        p.smoother_step(dev(bf.ravel(), dtype), dev(xf.ravel(), dtype), y)
+        check(f"S(x,b) Q{k} {N}^2 {dtype} variant {variant}", rel_l2(host(y), ref), bar)
+        edge = host(y).reshape(n1, n1)
+        assert np.all(edge[[0, -1], :] == 0.0) and np.all(edge[:, [0, -1]] == 0.0)
