@@ -352,12 +352,14 @@ int c0ip_problem::tail_level() {
   int cap = std::min(L, c0ip::kTailMaxLevels - 1);
   if (mg.tail_levels > 0) cap = std::min(cap, mg.tail_levels - 1);
   int nclass[c0ip::kTailMaxLevels] = {};
+  const bool ref = gamma == (double)(k * (k + 1));  // compile-time coefficients: no table in LDS
+  auto bytes = [&](int l) { return c0ip::tail_bytes(k, l, ref ? nullptr : nclass, (int)sizeof(T)); };
   for (int l = 0; l <= cap; ++l) {
     nclass[l] = lv[l]->rc.nclass;
-    if (c0ip::tail_bytes(k, l, nclass, (int)sizeof(T)) > lim) break;
+    if (bytes(l) > lim) break;
     if (l >= 1) t = l;
   }
-  if (t >= 1 && c0ip::configure_vtail<T>(k, c0ip::tail_bytes(k, t, nclass, (int)sizeof(T))) != hipSuccess) {
+  if (t >= 1 && (ref ? c0ip::configure_vtail_ref<T>(k, bytes(t)) : c0ip::configure_vtail<T>(k, bytes(t))) != hipSuccess) {
     (void)hipGetLastError();
     t = -1;
   }
@@ -385,6 +387,7 @@ void c0ip_problem::fill_tail(c0ip::TailParams<T>& P) {
   P.pre = mg.pre_steps;
   P.post = mg.post_steps;
   P.coarse_mode = mg.coarse_mode;
+  P.ref = work<T>(LT).coef.ref != nullptr;
 }
 
 template <typename T>

@@ -181,6 +181,7 @@ struct TailParams {
   const double* Ainv = nullptr;  // level-0 inverse (coarse_mode 0)
   T omega = 0;
   int pre = 1, post = 1, coarse_mode = 0;
+  bool ref = false;  // default penalty: compile-time coefficients (vtail_ref.hip)
 };
 // Per-level slot buffers: system s exists on level l iff s < nA[l]; its
 // vectors start at b[l] + s * stride[l] (x likewise).  A system's tail
@@ -193,13 +194,19 @@ struct TailIO {
   int nA[kTailMaxLevels] = {};
   const int* active = nullptr;
 };
-// LDS bytes of the tail kernel for degree k up to level LT (nclass per level).
+// LDS bytes of the tail kernel for degree k up to level LT (nclass per level,
+// or NULL for the default penalty's kernel).
 int tail_bytes(int k, int LT, const int* nclass, int elem_size);
+int tail_ref_bytes(int k, int LT, int elem_size);
 // Largest LDS a workgroup may use on the current device.
 int tail_lds_limit();
 // Allow the tail kernel of degree k `bytes` of dynamic LDS (before launch or capture).
 template <typename T>
 hipError_t configure_vtail(int k, int bytes);
+template <typename T>
+hipError_t configure_vtail_ref(int k, int bytes);
+template <typename T>
+hipError_t launch_vtail_ref(int k, const TailParams<T>& P, const TailIO<T>& io, int nsys, hipStream_t s);
 template <typename T>
 hipError_t launch_vtail(int k, const TailParams<T>& P, const TailIO<T>& io, int nsys, hipStream_t s);
 

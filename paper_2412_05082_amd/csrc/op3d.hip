@@ -70,11 +70,12 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // The boundary rows of B in a cheaper form than ref::boundary_b: a += the
-// difference of their coefficients from the periodic rows times the input, on the k nodes of the boundary cell.  The
-// whole rows reach three cells, for which the window along z leaves no
-// registers (Q3 128^3 float64 spills: 679 us against 418).  The difference
-// rounds at the size of the larger coefficient; for k <= 4 that does not show
-// in the results (at k = 5 it does).
+// difference of their coefficients from the periodic rows times the input, on
+// the k nodes of the boundary cell.  The whole rows reach three cells, for
+// which the window along z leaves no registers (Q3 128^3 float64 spills: 679
+// us against 418).  The difference rounds at the size of the larger
+// coefficient; for k <= 4 that does not show in the results (at k = 5 it
+// does).
 template <typename T, int K>
 __device__ __forceinline__ void add_boundary_b(T (&a)[K], const T* v, int c, int N) {
   static_assert(K <= 4, "rounding");

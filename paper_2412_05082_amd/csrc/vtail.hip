@@ -405,6 +405,7 @@ hipError_t vtail_k(const TailParams<T>& P, const TailIO<T>& io, int nsys, hipStr
 }  // namespace
 
 int tail_bytes(int k, int LT, const int* nclass, int elem_size) {
+  if (!nclass) return tail_ref_bytes(k, LT, elem_size);
   return tail_layout(k, LT, nclass, elem_size).bytes;
 }
 
@@ -427,6 +428,7 @@ hipError_t configure_vtail(int k, int bytes) {
 
 template <typename T>
 hipError_t launch_vtail(int k, const TailParams<T>& P, const TailIO<T>& io, int nsys, hipStream_t s) {
+  if (P.ref) return launch_vtail_ref<T>(k, P, io, nsys, s);
   switch (k) {
     case 2: return vtail_k<T, 2>(P, io, nsys, s);
     case 3: return vtail_k<T, 3>(P, io, nsys, s);

@@ -11,8 +11,9 @@ import pytest
 import scipy.linalg
 import torch
 
+import oracle as O
 import paper_2412_05082_amd as P
-from gpu_util import check, dev, fp32_tol, fp64_tol, host, rel_l2
+from gpu_util import check, dev, fp32_tol, fp64_tol, fp64_vcycle_tol, host, rel_l2, vectors
 
 pytestmark = pytest.mark.gpu
 OMEGA = 0.25
@@ -75,3 +76,23 @@ def test_operator_and_smoother_2d_tiles(k, N, dtype):
         check(f"S(x,b) Q{k} {N}^2 {dtype} variant {variant}", rel_l2(host(y), ref), bar)
         edge = host(y).reshape(n1, n1)
         assert np.all(edge[[0, -1], :] == 0.0) and np.all(edge[:, [0, -1]] == 0.0)
+
+
+@pytest.mark.parametrize("k,N", [(2, 16), (3, 32), (5, 8)])
+def test_other_penalty_2d(k, N):
+    """Another penalty constant takes the kernels with coefficient tables:
+    operator, smoother step and V-cycle against the oracle."""
+    gamma = 1.5 * k * (k + 1)
+    x, b = vectors(2, k, N)
+    A = O.assemble(2, k, N, gamma=gamma)
+    idx = O.patch_indices(2, k, N)
+    blocks = O.patch_blocks(O.assemble(2, k, N, gamma=gamma, bulk="diag"), idx)
+    p = P.Problem(2, N, k, gamma=gamma, omega=OMEGA, vcycle_dtype=P.C0IP_F64)
+    y = torch.empty(x.size, dtype=torch.float64, device="cuda")
+    p.apply_A(dev(x), y)
+    check("A x", rel_l2(host(y), A @ x), 1e-12)
+    p.smoother_step(dev(b), dev(x), y)
+    check("S(x,b)", rel_l2(host(y), O.avs_apply(A, blocks, idx, x, b, OMEGA)), fp64_tol(2, k, N))
+    p.vcycle(dev(b), y)
+    ref = O.Hierarchy(2, k, N, gamma=gamma, omega=OMEGA).vcycle(b)
+    check("V-cycle", rel_l2(host(y), ref), fp64_vcycle_tol(2, k, N))
