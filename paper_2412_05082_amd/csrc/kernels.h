@@ -121,6 +121,11 @@ hipError_t launch_mvs2d_colour(int k, int N, int colour, const LevelCoef<T>& c, 
 template <typename T>
 hipError_t launch_mvs2d_colour_exact(int k, int N, int colour, const LevelCoef<T>& c, const T* Aex, const T* b,
                                      const T* r, T* x, T omega, hipStream_t s);
+// Both for the default penalty (c.ref set): fast diagonalisation with Q and
+// lam, or exact local solves when Aex is given.
+template <typename T>
+hipError_t launch_mvs2d_colour_ref(int k, int N, int colour, const LevelCoef<T>& c, const T* Q, const T* lam,
+                                   const T* Aex, const T* b, const T* r, T* x, T omega, hipStream_t s);
 // One fused smoothing step S(x, b) (residual in LDS; x_out must not alias x).
 // variant: tile-size variant (0 = default; below avs2d_variants).  With ec:
 // the step starts from x + P ec instead (ec: coarse vector of the level

@@ -11,6 +11,7 @@
 
 #include "exact.h"
 #include "kernels.h"
+#include "mvs2d.h"
 #include "tiles.h"
 
 namespace c0ip {
@@ -214,47 +215,8 @@ hipError_t patch2d_atomic_k(int N, const LevelEig<T>& e, const T* r, T* xout, T 
 // vertices v = (2a + px, 2b + py) in [1, N-1]^2 with (a + b) mod 2 = rb;
 // their patches share no node and no entry of A couples two of them, so
 // each patch is solved once and its correction is added in place with a
-// plain store (no other patch of the colour touches its nodes).  The
-// vertices of a colour are numbered row by row of b; rows alternate
-// between two lengths.
-
-struct ColourRows {
-  int a_lo, a_hi, b_lo, nb;  // lattice ranges of a and b
-  int rb;
-  int cnt0, cnt1;            // patches in rows b_lo + 2i and b_lo + 2i + 1
-  int total;
-};
-
-__host__ __device__ inline int colour_row_count(int a_lo, int a_hi, int b, int rb) {
-  const int af = a_lo + (((rb - a_lo - b) % 2) + 2) % 2;
-  return af <= a_hi ? (a_hi - af) / 2 + 1 : 0;
-}
-
-inline ColourRows colour_rows(int N, int c) {
-  const int px = c & 1, py = (c >> 1) & 1;
-  ColourRows cr;
-  cr.rb = (c >> 2) & 1;
-  cr.a_lo = px == 0 ? 1 : 0;
-  cr.a_hi = (N - 1 - px) / 2;
-  cr.b_lo = py == 0 ? 1 : 0;
-  const int b_hi = (N - 1 - py) / 2;
-  cr.nb = b_hi >= cr.b_lo ? b_hi - cr.b_lo + 1 : 0;
-  cr.cnt0 = colour_row_count(cr.a_lo, cr.a_hi, cr.b_lo, cr.rb);
-  cr.cnt1 = colour_row_count(cr.a_lo, cr.a_hi, cr.b_lo + 1, cr.rb);
-  cr.total = (cr.nb / 2) * (cr.cnt0 + cr.cnt1) + (cr.nb % 2) * cr.cnt0;
-  return cr;
-}
-
-// vertex (vx, vy) of the patch with number q of the colour
-__device__ __forceinline__ void colour_vertex(const ColourRows& cr, int px, int py, int q, int& vx, int& vy) {
-  const int pair = cr.cnt0 + cr.cnt1;
-  const int i = q / pair, rem = q - i * pair;
-  const int b = cr.b_lo + 2 * i + (rem >= cr.cnt0 ? 1 : 0);
-  const int t = rem >= cr.cnt0 ? rem - cr.cnt0 : rem;
-  const int af = cr.a_lo + (((cr.rb - cr.a_lo - b) % 2) + 2) % 2;
-  vx = 2 * (af + 2 * t) + px;
-  vy = 2 * b + py;
-}
+// plain store (no other patch of the colour touches its nodes).  These
+// kernels read the coefficient tables; the default penalty takes mvs2d.hip.
 
 // Patches per workgroup of the colour kernel and its LDS strips.  A patch's
 // residual rows (its (2k-1)^2 interior nodes) reach, through the bands of
@@ -690,6 +652,7 @@ hipError_t launch_patch2d_atomic(int k, int N, const LevelEig<T>& e, const T* r,
 template <typename T>
 hipError_t launch_mvs2d_colour(int k, int N, int colour, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b,
                                const T* r, T* x, T omega, hipStream_t s) {
+  if (c.ref) return launch_mvs2d_colour_ref<T>(k, N, colour, c, e.Q, e.lam, nullptr, b, r, x, omega, s);
 #define CALL(K) mvs2d_colour_k<T, K, false>(N, colour, c, e.Q, e.lam, nullptr, b, r, x, omega, s)
   C0IP_DISPATCH_K(k, CALL)
 #undef CALL
@@ -706,6 +669,7 @@ hipError_t launch_patch2d_exact(int k, int N, const T* Aex, const T* r, const T*
 template <typename T>
 hipError_t launch_mvs2d_colour_exact(int k, int N, int colour, const LevelCoef<T>& c, const T* Aex, const T* b,
                                      const T* r, T* x, T omega, hipStream_t s) {
+  if (c.ref) return launch_mvs2d_colour_ref<T>(k, N, colour, c, nullptr, nullptr, Aex, b, r, x, omega, s);
 #define CALL(K) mvs2d_colour_k<T, K, true>(N, colour, c, nullptr, nullptr, Aex, b, r, x, omega, s)
   C0IP_DISPATCH_K(k, CALL)
 #undef CALL

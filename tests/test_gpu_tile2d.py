@@ -13,7 +13,7 @@ import torch
 
 import oracle as O
 import paper_2412_05082_amd as P
-from gpu_util import check, dev, fp32_tol, fp64_tol, fp64_vcycle_tol, host, rel_l2, vectors
+from gpu_util import check, dev, fp32_mvs_tol, fp32_tol, fp64_mvs_tol, fp64_tol, fp64_vcycle_tol, host, rel_l2, vectors
 
 pytestmark = pytest.mark.gpu
 OMEGA = 0.25
@@ -96,3 +96,28 @@ def test_other_penalty_2d(k, N):
     p.vcycle(dev(b), y)
     ref = O.Hierarchy(2, k, N, gamma=gamma, omega=OMEGA).vcycle(b)
     check("V-cycle", rel_l2(host(y), ref), fp64_vcycle_tol(2, k, N))
+
+
+@pytest.mark.parametrize("k,N", [(2, 2), (2, 64), (3, 8), (3, 64), (4, 4), (4, 32), (5, 16), (6, 16), (7, 2), (7, 16)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_multiplicative_step_2d(k, N, dtype):
+    """The coloured step with the residual in the colour's launch: one patch
+    (seven empty colours), patches that fill part of a workgroup, and several
+    workgroups per colour."""
+    n1, n = k * N + 1, 2 * k - 1
+    rng = np.random.default_rng(100 * k + N)
+    x, b = (np.pad(rng.uniform(-1.0, 1.0, (n1 - 2, n1 - 2)).astype(np.float32).astype(np.float64), 1)
+            for _ in range(2))
+    _, _, _, E, lam = _factors(k, N)
+    v = np.repeat(np.arange(1, N), n)
+    ref = x.copy()
+    for c in range(8):
+        on = (((v[:, None] // 2 + v[None, :] // 2) % 2 == c // 4) & (v[:, None] % 2 == c // 2 % 2)
+              & (v[None, :] % 2 == c % 2))
+        ref = ref + E.T @ (on * (E @ (b - _apply(k, N, ref)) @ E.T) / (lam[:, None] + lam[None, :])) @ E
+    p = P.Problem(2, N, k, omega=1.0, smoother=1, mvs_residual=1)
+    y = torch.full((n1 * n1,), 7.0, dtype=dtype, device="cuda")
+    p.smoother_step(dev(b.ravel(), dtype), dev(x.ravel(), dtype), y)
+    small = min(N, 8)
+    bar = fp64_mvs_tol(2, k, small) if dtype == torch.float64 else fp32_mvs_tol(2, k, small, 1.0)
+    check(f"MVS Q{k} {N}^2 {dtype}", rel_l2(host(y), ref.ravel()), bar)
