@@ -323,11 +323,14 @@ void c0ip_problem::smooth_mvs(int l, const T* b, T* x, T* r, int steps, bool x_i
   //   (1.64 M) 398 against 383, Q3 512^2 (2.36 M) 357 against 315, Q7 256^2 (3.21 M) 1282 against 925.
   constexpr int64_t kMvsInLaunchBelow = int64_t(3) << 19;
   const bool in_launch = (w.coef.ref && k <= 6) || lv[l]->ntot < kMvsInLaunchBelow;
+  // 3D, default penalty, up to k = 4: always in-launch (Q2 step against a residual pass per colour, us: 128^3
+  // float32 1100 against 1590, 8^3 82 against 265).
+  const bool ref3 = dim == 3 && w.coef.ref && k <= 4;
   for (int s = 0; s < steps; ++s)
     for (int c = 0; c < ncol; ++c) {
       const bool zero = s == 0 && c == 0 && x_is_zero;
       if (zero) check(c0ip::launch_fill_t<T>(lv[l]->ntot, T(0), x, stream), "fill");
-      const bool fused = dim == 2 && (mg.mvs_residual == 1 || (mg.mvs_residual == 0 && in_launch));
+      const bool fused = ref3 || (dim == 2 && (mg.mvs_residual == 1 || (mg.mvs_residual == 0 && in_launch)));
       const T* rc = zero ? b : (fused ? nullptr : r);
       if (!zero && !fused) check(c0ip::launch_apply<T, T>(dim, k, Nl, w.coef, x, b, r, stream), "residual");
       if (dim == 2 && mg.local_solver == 1)
@@ -335,6 +338,9 @@ void c0ip_problem::smooth_mvs(int l, const T* b, T* x, T* r, int steps, bool x_i
               "multiplicative colour");
       else if (dim == 2)
         check(c0ip::launch_mvs2d_colour<T>(k, Nl, c, w.coef, w.eig, b, rc, x, om, stream),
+              "multiplicative smoother colour");
+      else if (ref3)
+        check(c0ip::launch_mvs3d_colour_ref<T>(k, Nl, c, w.coef, w.eig, b, rc, x, om, stream),
               "multiplicative smoother colour");
       else
         check(c0ip::launch_mvs3d_colour<T>(k, Nl, c, w.eig, rc, x, om, stream), "multiplicative smoother colour");

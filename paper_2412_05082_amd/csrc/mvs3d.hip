@@ -8,7 +8,8 @@
 // of cc; within a plane the vertices with (a + b) mod 2 = (rb - cc) mod 2,
 // row by row of b (rows alternate between two lengths, and so do planes).
 // Local solve: fast diagonalisation (eq. inverse) as three passes of 1D
-// transforms along x, y and z.
+// transforms along x, y and z.  The default penalty up to k = 4 takes
+// mvs3d_ref.hip, which forms the residual in the same launch.
 #include "mvs3d.h"
 #include "tiles.h"
 
@@ -17,17 +18,6 @@ namespace {
 
 constexpr int kThreads = tile::kThreads;
 using tile::variant;
-
-struct Lat {
-  int lo, hi;  // lattice index range along one axis
-};
-
-__host__ __device__ inline Lat lat(int N, int par) { return {par == 0 ? 1 : 0, (N - 1 - par) / 2}; }
-
-__host__ __device__ inline int row_count(Lat a, int b, int par) {
-  const int af = a.lo + (((par - a.lo - b) % 2) + 2) % 2;
-  return af <= a.hi ? (a.hi - af) / 2 + 1 : 0;
-}
 
 // vertices of one plane whose (a + b) has parity par
 __host__ __device__ inline int plane_count(Lat a, Lat b, int par) {
