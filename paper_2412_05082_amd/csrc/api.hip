@@ -324,7 +324,7 @@ void c0ip_problem::smooth_mvs(int l, const T* b, T* x, T* r, int steps, bool x_i
   constexpr int64_t kMvsInLaunchBelow = int64_t(3) << 19;
   const bool in_launch = (w.coef.ref && k <= 6) || lv[l]->ntot < kMvsInLaunchBelow;
   // 3D, default penalty, up to k = 4: always in-launch (Q2 step against a residual pass per colour, us: 128^3
-  // float32 1100 against 1590, 8^3 82 against 265).
+  // float32 1100 against 1623, 8^3 82 against 268).
   const bool ref3 = dim == 3 && w.coef.ref && k <= 4;
   for (int s = 0; s < steps; ++s)
     for (int c = 0; c < ncol; ++c) {

@@ -160,7 +160,10 @@ hipError_t launch_prolong2d(int k, int Nc, const T* table, const T* ec, const T*
                             int nsys = 1, int64_t zc = 0, int64_t zf = 0, const int* active = nullptr);
 template <typename Tin, typename T>
 hipError_t launch_apply3d(int k, int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s);
-// z-streaming operator with per-lane band loops (any k; used for k >= 5).
+// The same on boxes of cells (default penalty; any k).
+template <typename Tin, typename T>
+hipError_t launch_apply3d_box(int k, int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s);
+// z-streaming operator with per-lane band loops (any k; used for other penalties).
 template <typename Tin, typename T>
 hipError_t launch_apply3d_wide(int k, int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s);
 template <typename T>

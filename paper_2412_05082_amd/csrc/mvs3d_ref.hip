@@ -3,7 +3,7 @@
 //   x <- x + omega * sum_{v of the colour} R_v^T A~_v^{-1} R_v (b - A x).
 // A separate residual pass computes all of b - A x although a colour's
 // patches hold a fifth of its nodes, and on a coarse mesh its z march is one
-// long serial chain in a few workgroups (11 us at 8^3 to 32^3).
+// long serial chain in a few workgroups (11 us at 8^3 to 32^3; 6 us on boxes).
 //
 // A workgroup owns P consecutive patches of one row of the colour (same vy,
 // vz, 4 cells apart in x).  In the grouped form of the operator,
@@ -16,9 +16,9 @@
 // the local solve, whose other transforms run line by line in registers.
 //
 // One step (16 colours) against a residual pass and a launch of local solves
-// per colour: Q2 128^3 float32 1590 -> 1100 us, Q2 32^3 265 -> 82, Q3 64^3
-// float64 1990 -> 1275; it is bound by instruction issue and, on the finest
-// meshes, by reading x about 1.5 times per colour.
+// per colour: Q2 128^3 float32 1623 -> 1100 us, Q2 8^3 268 -> 82; it is bound
+// by instruction issue and, on the finest meshes, by reading x about 1.5 times
+// per colour.
 //
 // Why in place is safe: patches of one colour lie 4 cells apart along an
 // axis or 2 along two, so no node that a patch's residual depends on is an
@@ -86,12 +86,6 @@ __device__ __forceinline__ void patch_b(const T* w, T (&o)[2 * K - 1], int v, in
   for (int p = 0; p < K; ++p) o[K - 1 + p] = c[p];
 }
 
-// q / d as a high product with magic(d) = 2^32 / d rounded up: exact while q d < 2^32 (d = 1: 0 stands for 2^32),
-// which meshes that fit in memory keep by far.  A division by a kernel argument would take some 40 vector
-// instructions of every wave.
-__host__ __device__ inline unsigned magic(unsigned d) { return d == 1 ? 0u : 0xffffffffu / d + 1; }
-__device__ __forceinline__ unsigned quotient(unsigned q, unsigned m) { return m ? __umulhi(q, m) : q; }
-
 template <typename T, int K, int NTH, bool RES>
 __global__ __launch_bounds__(NTH) void mvs3d_colour_ref_kernel(
     const T* __restrict__ b, T* __restrict__ x, int N, int n1, int colour, int nxc, unsigned mx, int nb, unsigned mb, T scale,
@@ -104,7 +98,7 @@ __global__ __launch_bounds__(NTH) void mvs3d_colour_ref_kernel(
   __shared__ T sLam[4 * n];
   const int t = threadIdx.x;
   // this workgroup's row of the colour and its patches there
-  const unsigned q = tile2::xcd_order(blockIdx.x, gridDim.x), yz = quotient(q, mx), cb = quotient(yz, mb);
+  const unsigned q = tile2::xcd_order(blockIdx.x, gridDim.x), yz = tile2::quotient(q, mx), cb = tile2::quotient(yz, mb);
   const int px = colour & 1, py = (colour >> 1) & 1, pz = (colour >> 2) & 1;
   const Lat la = lat(N, px);
   const int lb = lat(N, py).lo + (int)(yz - cb * nb), lc = lat(N, pz).lo + (int)cb;
@@ -367,7 +361,7 @@ hipError_t mvs3d_ref_k(int N, int colour, const LevelCoef<T>& c, const LevelEig<
   const int nb = bb.hi - bb.lo + 1, nc = cc.hi - cc.lo + 1, na = (a.hi - a.lo) / 2 + 1;
   if (a.hi < a.lo || nb <= 0 || nc <= 0) return hipSuccess;
   const int nxc = (na + G::P - 1) / G::P, total = nxc * nb * nc;
-  const unsigned mx = magic(nxc), mb = magic(nb);
+  const unsigned mx = tile2::magic(nxc), mb = tile2::magic(nb);
   if (r)
     mvs3d_colour_ref_kernel<T, K, G::NTH, false><<<total, G::NTH, 0, s>>>(r, x, N, K * N + 1, colour, nxc, mx, nb, mb,
                                                                      c.hinv, e.Q, e.lam, omega);

@@ -7,7 +7,8 @@
 //   S3 = 2 (L_y (X M_x) + M_y (X L_x)),
 // the output is Y = M_z S1 + B_z S2 + L_z S3.
 //
-// A workgroup owns a TY x TX column of output nodes (whole cells) over a
+// Up to degree 4 and from 64^3 cells on (32^3 at k = 2; op3d_box.hip below):
+// a workgroup owns a TY x TX column of output nodes (whole cells) over a
 // chunk of z cells and streams through the planes of the chunk plus a
 // 2k-plane halo on each side:
 //   * the plane is staged once in LDS with a 2k-node halo in x and y (the
@@ -42,6 +43,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "faces3d.h"
 #include "kernels.h"
 #include "refband.h"
 #include "tiles.h"
@@ -352,27 +354,6 @@ __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T*
   }
 }
 
-// Zeros on the faces x = kN, y = kN, z = kN (boundary nodes that no tile
-// owns): face element f of 3 n1^2, 16 per thread.
-template <typename T, int NTH>
-__device__ __forceinline__ void zero_faces(T* __restrict__ y, int n1, int fb) {
-  const int NK = n1 - 1;
-  const int64_t nf = (int64_t)n1 * n1;
-  for (int q = 0; q < 16; ++q) {
-    const int64_t f = ((int64_t)fb * 16 + q) * NTH + threadIdx.x;
-    if (f >= 3 * nf) return;
-    const int face = (int)(f / nf);
-    const int64_t rem = f - face * nf;
-    const int u = (int)(rem % n1), w = (int)(rem / n1);
-    const int gx = face == 0 ? NK : u, gy = face == 0 ? u : (face == 1 ? NK : w), gz = face == 2 ? NK : w;
-    y[((size_t)gz * n1 + gy) * n1 + gx] = T(0);
-  }
-}
-template <int NTH>
-inline int face_blocks(int n1) {
-  return (int)((3 * (int64_t)n1 * n1 + 16 * NTH - 1) / (16 * NTH));
-}
-
 // One workgroup per (tile, z chunk), each XCD walking a contiguous band of
 // them (x fastest, then y: neighbouring tiles share halos in that XCD's L2),
 // then the workgroups that zero the faces.
@@ -411,8 +392,8 @@ hipError_t apply3d_g(int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* 
   const int tx = (N + G::TXC - 1) / G::TXC, ty = (N + G::TYC - 1) / G::TYC;
   // z chunks: 1024 workgroups (what the chip holds at 3 waves per SIMD), down
   // to one cell per chunk: a chunk recomputes 3k + 1 halo planes, but below
-  // 1024 workgroups the march along z sets the time (3D Q3 32^3 float64: 63 us
-  // at 8 cells per chunk, 43 at 4, 33 at 1).  Twice as many for Q3 float64
+  // 1024 workgroups the march along z sets the time (3D Q3 32^3 float64, which
+  // boxes take now: 63 us at 8 cells per chunk, 43 at 4, 33 at 1).  Twice as many for Q3 float64
   // from 128^3: there the halos come from HBM once the workgroups of a plane
   // have drifted apart along a long march (128^3: 476 us against 420; 256^3:
   // 4239 against 3222; float32 and the other degrees are slower by up to 15 %).
@@ -434,6 +415,14 @@ hipError_t apply3d_g(int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* 
 template <typename Tin, typename T>
 hipError_t launch_apply3d(int k, int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s) {
   if (!c.ref) return launch_apply3d_wide<Tin, T>(k, N, c, x, b, y, s);  // not the default penalty
+  // Small meshes and high degrees on boxes (op3d_box.hip): below 64 cells the march along z, a plane after the
+  // other, sets the time (float64, march against boxes, us: Q2 16^3 11.8 against 6.4, 32^3 12.5 against 12.5,
+  // 64^3 30 against 54; Q3 16^3 25.6 against 7.5, 32^3 34 against 24, 64^3 82 against 145; Q4 32^3 91 against 52,
+  // 64^3 234 against 368); from degree 5 the march's window does not fit the registers (Q5 32^3 with bands
+  // in loops 1267 us against 184, 8^3 433 against 11).  Boxes address 4k + 1 planes with 31 bits.
+  const bool box = k >= 5 || N <= (k == 2 ? 16 : 32);
+  if (box && (4.0 * k + 1) * (k * N + 1) * (k * N + 1) * sizeof(Tin) < 2147483648.0)
+    return launch_apply3d_box<Tin, T>(k, N, c, x, b, y, s);
   // raw buffer offsets of a plane must stay below 2^31 bytes
   if ((double)(k * N + 1) * (k * N + 1) * sizeof(T) >= 2147483648.0) return hipErrorInvalidValue;
   switch (k) {

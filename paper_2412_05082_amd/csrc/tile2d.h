@@ -36,6 +36,13 @@ __device__ __forceinline__ int xcd_order(int L, int total) {
   return c * (total >> 3) + min(c, total & 7) + (L >> 3);
 }
 
+// q / d as a high product with magic(d) = 2^32 / d rounded up (d = 1: 0
+// stands for 2^32): exact while q d < 2^32, which tile numbers of meshes that
+// fit in memory keep by far.  A division by a kernel argument would take some
+// 40 vector instructions of every wave.
+__host__ __device__ inline unsigned magic(unsigned d) { return d == 1 ? 0u : 0xffffffffu / d + 1; }
+__device__ __forceinline__ unsigned quotient(unsigned q, unsigned m) { return m ? __umulhi(q, m) : q; }
+
 // Operator tile: TXC x TYC cells, NTH threads, x items of CW cells.
 template <int K_, int TXC_, int TYC_, int NTH_, int CW_>
 struct Op {
