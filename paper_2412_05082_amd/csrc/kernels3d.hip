@@ -1,5 +1,5 @@
-// 3D kernels: matrix-free C0IP operator and the additive vertex-patch
-// smoother with fast-diagonalisation local solves, for gfx950.
+// 3D matrix-free C0IP operator with coefficient tables, for gfx950: the form
+// that every penalty but the default one takes.
 //
 // Operator (Sec. 4, eq. c0iptensorvp3D, used globally on the Cartesian
 // mesh), first factor along x:
@@ -12,13 +12,6 @@
 // per plane it stages X on the tile plus a 2k halo in LDS, runs the x- and
 // y-sweeps, and pushes S1, S2, S3 of its own column into register windows
 // of 4k+1 planes, from which the z-sweep emits one output plane.
-//
-// Smoother (Sec. 3, eq. localsolverbila in 3D, eq. inverse):
-// owner-computes over tiles of TC^3 cells.  The (TC+1)^3 patches touching
-// a tile are solved in the 8 classes of vertex parity; patches of one
-// class are disjoint, so their damped corrections are added to an LDS
-// accumulator of the owned nodes without conflicts.  Each contraction
-// is applied in place along lines of the patch.
 #include "kernels.h"
 
 namespace c0ip {
@@ -177,165 +170,11 @@ hipError_t apply3d_k(int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* 
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ smoother
-
-__device__ __forceinline__ int variant(int v, int N) { return (v == 1 ? 1 : 0) | (v == N - 1 ? 2 : 0); }
-
-template <int K> struct PatchTile3D;
-template <> struct PatchTile3D<2> { static constexpr int TC = 4; };
-template <> struct PatchTile3D<3> { static constexpr int TC = 3; };
-template <> struct PatchTile3D<4> { static constexpr int TC = 2; };
-template <> struct PatchTile3D<5> { static constexpr int TC = 1; };
-template <> struct PatchTile3D<6> { static constexpr int TC = 1; };
-template <> struct PatchTile3D<7> { static constexpr int TC = 1; };
-
-template <typename T, int K, int TC>
-__global__ __launch_bounds__(kThreads) void patch3d_kernel(const T* __restrict__ r, const T* __restrict__ xin,
-                                                           T* __restrict__ xout, int N, int n1,
-                                                           const T* __restrict__ Qg, const T* __restrict__ lamg,
-                                                           T omega) {
-  constexpr int n = 2 * K - 1, NN = n * n, N3 = NN * n, NP = TC + 1, S = (TC + 2) * K - 1;
-  constexpr int PB = ((NP + 1) / 2) * ((NP + 1) / 2) * ((NP + 1) / 2);  // largest parity class
-  constexpr int OW = TC * K + 1;
-  __shared__ T sR[S * S * S];
-  __shared__ T sP[PB * N3];
-  __shared__ T sAcc[OW * OW * OW];
-  __shared__ T sQ[4 * NN];
-  __shared__ T sLam[4 * n];
-  const int c0[3] = {(int)blockIdx.x * TC, (int)blockIdx.y * TC, (int)blockIdx.z * TC};
-  const int o0 = (c0[0] - 1) * K + 1, o1 = (c0[1] - 1) * K + 1, o2 = (c0[2] - 1) * K + 1;
-  const size_t plane = (size_t)n1 * n1;
-  for (int e = threadIdx.x; e < S * S * S; e += kThreads) {
-    const int i = e % S, j = (e / S) % S, l = e / (S * S);
-    const int g0 = o0 + i, g1 = o1 + j, g2 = o2 + l;
-    const bool in = g0 >= 1 && g0 <= n1 - 2 && g1 >= 1 && g1 <= n1 - 2 && g2 >= 1 && g2 <= n1 - 2;
-    sR[e] = in ? r[(size_t)g2 * plane + (size_t)g1 * n1 + g0] : T(0);
-  }
-  for (int e = threadIdx.x; e < OW * OW * OW; e += kThreads) sAcc[e] = T(0);
-  for (int e = threadIdx.x; e < 4 * NN; e += kThreads) sQ[e] = Qg[e];
-  for (int e = threadIdx.x; e < 4 * n; e += kThreads) sLam[e] = lamg[e];
-  __syncthreads();
-  for (int par = 0; par < 8; ++par) {
-    // patches of this tile whose vertex parity is par, numbered 0..np-1
-    const int px = par & 1, py = (par >> 1) & 1, pz = par >> 2;
-    const int vx0 = c0[0] + ((px - c0[0]) % 2 + 2) % 2, vy0 = c0[1] + ((py - c0[1]) % 2 + 2) % 2,
-              vz0 = c0[2] + ((pz - c0[2]) % 2 + 2) % 2;
-    const int cx = vx0 <= c0[0] + TC ? (c0[0] + TC - vx0) / 2 + 1 : 0;
-    const int cyn = vy0 <= c0[1] + TC ? (c0[1] + TC - vy0) / 2 + 1 : 0;
-    const int czn = vz0 <= c0[2] + TC ? (c0[2] + TC - vz0) / 2 + 1 : 0;
-    const int np = cx * cyn * czn;
-    // gather R_v r for each patch into sP
-    for (int e = threadIdx.x; e < np * N3; e += kThreads) {
-      const int pi = e / N3, t = e - pi * N3;
-      const int a0 = t % n, a1 = (t / n) % n, a2 = t / NN;
-      const int vx = vx0 + 2 * (pi % cx), vy = vy0 + 2 * ((pi / cx) % cyn), vz = vz0 + 2 * (pi / (cx * cyn));
-      // region index of node (vx-1)k+1+a0 etc.
-      const int i = (vx - c0[0]) * K + a0, j = (vy - c0[1]) * K + a1, l = (vz - c0[2]) * K + a2;
-      sP[e] = sR[(l * S + j) * S + i];
-    }
-    __syncthreads();
-    // six in-place line passes; pass d (0,1,2 forward along x,y,z; 3,4,5 back along z,y,x)
-    for (int pass = 0; pass < 6; ++pass) {
-      const int ax = pass < 3 ? pass : 5 - pass;
-      const bool fwd = pass < 3;
-      for (int e = threadIdx.x; e < np * NN; e += kThreads) {
-        const int pi = e / NN, t = e - pi * NN;
-        const int u0 = t % n, u1 = t / n;  // the two other coordinates
-        const int vx = vx0 + 2 * (pi % cx), vy = vy0 + 2 * ((pi / cx) % cyn), vz = vz0 + 2 * (pi / (cx * cyn));
-        const int vv = ax == 0 ? vx : (ax == 1 ? vy : vz);
-        const T* q = sQ + variant(vv, N) * NN;
-        int base, stride;
-        if (ax == 0) { base = u0 * n + u1 * NN; stride = 1; }
-        else if (ax == 1) { base = u0 + u1 * NN; stride = n; }
-        else { base = u0 + u1 * n; stride = NN; }
-        T* line = sP + pi * N3 + base;
-        T in[n], out[n];
-#pragma unroll
-        for (int a = 0; a < n; ++a) in[a] = line[a * stride];
-        if (fwd) {
-#pragma unroll
-          for (int c = 0; c < n; ++c) {
-            T sacc = 0;
-#pragma unroll
-            for (int a = 0; a < n; ++a) sacc += q[a * n + c] * in[a];
-            out[c] = sacc;
-          }
-          if (ax == 2) {  // divide by lambda_x + lambda_y + lambda_z, then back along z
-            const T lxy = sLam[variant(vx, N) * n + u0] + sLam[variant(vy, N) * n + u1];
-            const T* lz = sLam + variant(vz, N) * n;
-#pragma unroll
-            for (int c = 0; c < n; ++c) in[c] = out[c] / (lxy + lz[c]);
-#pragma unroll
-            for (int a = 0; a < n; ++a) {
-              T sacc = 0;
-#pragma unroll
-              for (int c = 0; c < n; ++c) sacc += q[a * n + c] * in[c];
-              out[a] = sacc;
-            }
-          }
-        } else {
-#pragma unroll
-          for (int a = 0; a < n; ++a) {
-            T sacc = 0;
-#pragma unroll
-            for (int c = 0; c < n; ++c) sacc += q[a * n + c] * in[c];
-            out[a] = sacc;
-          }
-        }
-#pragma unroll
-        for (int a = 0; a < n; ++a) line[a * stride] = out[a];
-      }
-      if (pass == 2) ++pass;  // z forward and back were fused
-      __syncthreads();
-    }
-    // add the corrections on owned nodes (patches of one class are disjoint)
-    for (int e = threadIdx.x; e < np * N3; e += kThreads) {
-      const int pi = e / N3, t = e - pi * N3;
-      const int a0 = t % n, a1 = (t / n) % n, a2 = t / NN;
-      const int vx = vx0 + 2 * (pi % cx), vy = vy0 + 2 * ((pi / cx) % cyn), vz = vz0 + 2 * (pi / (cx * cyn));
-      if (vx < 1 || vx > N - 1 || vy < 1 || vy > N - 1 || vz < 1 || vz > N - 1) continue;
-      const int g0 = (vx - 1) * K + 1 + a0 - c0[0] * K, g1 = (vy - 1) * K + 1 + a1 - c0[1] * K,
-                g2 = (vz - 1) * K + 1 + a2 - c0[2] * K;  // owned-local
-      if (g0 < 0 || g0 >= TC * K || g1 < 0 || g1 >= TC * K || g2 < 0 || g2 >= TC * K) continue;
-      sAcc[(g2 * OW + g1) * OW + g0] += sP[e];
-    }
-    __syncthreads();
-  }
-  const int gx1 = (c0[0] + TC >= N) ? n1 : (c0[0] + TC) * K;
-  const int gy1 = (c0[1] + TC >= N) ? n1 : (c0[1] + TC) * K;
-  const int gz1 = (c0[2] + TC >= N) ? n1 : (c0[2] + TC) * K;
-  for (int e = threadIdx.x; e < OW * OW * OW; e += kThreads) {
-    const int i = e % OW, j = (e / OW) % OW, l = e / (OW * OW);
-    const int g0 = c0[0] * K + i, g1 = c0[1] * K + j, g2 = c0[2] * K + l;
-    if (g0 >= gx1 || g1 >= gy1 || g2 >= gz1) continue;
-    const size_t idx = (size_t)g2 * plane + (size_t)g1 * n1 + g0;
-    const bool bnd = g0 == 0 || g0 == n1 - 1 || g1 == 0 || g1 == n1 - 1 || g2 == 0 || g2 == n1 - 1;
-    xout[idx] = bnd ? T(0) : (xin ? xin[idx] : T(0)) + omega * sAcc[e];
-  }
-}
-
-template <typename T, int K>
-hipError_t patch3d_k(int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega, hipStream_t s) {
-  constexpr int TC = PatchTile3D<K>::TC;
-  const int n1 = K * N + 1;
-  const int nt = (N + TC - 1) / TC;
-  patch3d_kernel<T, K, TC><<<dim3(nt, nt, nt), kThreads, 0, s>>>(r, xin, xout, N, n1, e.Q, e.lam, omega);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 template <typename Tin, typename T>
 hipError_t launch_apply3d_wide(int k, int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s) {
 #define CALL(K) apply3d_k<Tin, T, K>(N, c, x, b, y, s)
-  C0IP_DISPATCH_K(k, CALL)
-#undef CALL
-}
-
-template <typename T>
-hipError_t launch_patch3d_wide(int k, int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega,
-                          hipStream_t s) {
-#define CALL(K) patch3d_k<T, K>(N, e, r, xin, xout, omega, s)
   C0IP_DISPATCH_K(k, CALL)
 #undef CALL
 }
@@ -346,9 +185,4 @@ template hipError_t launch_apply3d_wide<float, double>(int, int, const LevelCoef
                                                   const double*, double*, hipStream_t);
 template hipError_t launch_apply3d_wide<float, float>(int, int, const LevelCoef<float>&, const float*, const float*,
                                                  float*, hipStream_t);
-template hipError_t launch_patch3d_wide<double>(int, int, const LevelEig<double>&, const double*, const double*,
-                                           double*, double, hipStream_t);
-template hipError_t launch_patch3d_wide<float>(int, int, const LevelEig<float>&, const float*, const float*, float*,
-                                          float, hipStream_t);
-
 }  // namespace c0ip

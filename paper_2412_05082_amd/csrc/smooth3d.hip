@@ -351,7 +351,7 @@ hipError_t launch_patch3d(int k, int N, const LevelEig<T>& e, const T* r, const 
     case 2: return smooth3d_g<T, typename SmoothCfg<T, 2>::G>(N, e, r, xin, xout, omega, s);
     case 3: return smooth3d_g<T, typename SmoothCfg<T, 3>::G>(N, e, r, xin, xout, omega, s);
     case 4: return smooth3d_g<T, typename SmoothCfg<T, 4>::G>(N, e, r, xin, xout, omega, s);
-    default: return launch_patch3d_wide<T>(k, N, e, r, xin, xout, omega, s);
+    default: return launch_patch3d_box<T>(k, N, e, r, xin, xout, omega, s);
   }
 }
 
