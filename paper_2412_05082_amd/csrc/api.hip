@@ -72,7 +72,7 @@ template <typename T>
 struct LevelWork {
   DevBuf<T> tab, Q, lam, ptab;  // coefficient table, eigenbases, prolongation table
   DevBuf<T> tabref;             // the table scaled to h = 1 (default penalty only)
-  DevBuf<T> x, b, r, scratch;   // V-cycle vectors and transfer scratch
+  DevBuf<T> x, b, r;            // V-cycle vectors
   DevBuf<T> t;                  // 2D: second iterate buffer (smoothing steps are out of place)
   DevBuf<T> Aex;                // exact local solver: one dense patch inverse per boundary type
   c0ip::LevelCoef<T> coef;
@@ -217,11 +217,6 @@ void c0ip_problem::prepare(int l) {
   w.b.alloc(L_.ntot);
   w.r.alloc(L_.ntot);
   if (dim == 2) w.t.alloc(L_.ntot);
-  if (l > 0) {
-    const int64_t nf = L_.n1, nc = lv[l - 1]->n1;
-    const int64_t s = dim == 2 ? nf * nc : 2 * nf * nf * nc;
-    w.scratch.alloc(s);
-  }
   w.ready = true;
 }
 
@@ -482,10 +477,10 @@ void c0ip_problem::mg_level(int l, const T* b, T* x) {
   }
   smooth<T>(l, b, x, mg.pre_steps, true);
   check(c0ip::launch_apply<T, T>(dim, k, lv[l]->N, w.coef, x, b, w.r.p, stream), "residual");
-  check(c0ip::launch_restrict<T>(dim, k, lv[l - 1]->N, w.ptab.p, w.r.p, wc.b.p, w.scratch.p, stream), "restrict");
+  check(c0ip::launch_restrict<T>(dim, k, lv[l - 1]->N, w.ptab.p, w.r.p, wc.b.p, stream), "restrict");
   mg_level<T>(l - 1, wc.b.p, wc.x.p);
   {
-    check(c0ip::launch_prolong_add<T>(dim, k, lv[l - 1]->N, w.ptab.p, wc.x.p, x, w.scratch.p, stream), "prolong");
+    check(c0ip::launch_prolong_add<T>(dim, k, lv[l - 1]->N, w.ptab.p, wc.x.p, x, stream), "prolong");
     smooth<T>(l, b, x, mg.post_steps, false);
   }
 }

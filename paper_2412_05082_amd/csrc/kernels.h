@@ -37,14 +37,16 @@ template <typename T>
 hipError_t launch_patch_smooth(int dim, int k, int N, const LevelEig<T>& e, const T* r, const T* x_in,
                                T* x_out, T omega, hipStream_t s);
 
-// Grid transfers (tensor-product 1D embedding, table [2][k][k+1]).
-// restrict: bc = P^T rf;  prolong: xf (+)= P ec.  scratch >= n1f^(dim-1) * n1c elements.
+// Grid transfers (tensor-product 1D embedding, table [2][k][k+1]; 3D uses
+// the same table's compile-time form): bc = P^T rf; xf += P ec.
 template <typename T>
-hipError_t launch_restrict(int dim, int k, int Nc, const T* table, const T* rf, T* bc, T* scratch,
-                           hipStream_t s);
+hipError_t launch_restrict(int dim, int k, int Nc, const T* table, const T* rf, T* bc, hipStream_t s);
 template <typename T>
-hipError_t launch_prolong_add(int dim, int k, int Nc, const T* table, const T* ec, T* xf, T* scratch,
-                              hipStream_t s);
+hipError_t launch_prolong_add(int dim, int k, int Nc, const T* table, const T* ec, T* xf, hipStream_t s);
+template <typename T>
+hipError_t launch_restrict3d(int k, int Nc, const T* rf, T* bc, hipStream_t s);
+template <typename T>
+hipError_t launch_prolong3d(int k, int Nc, const T* ec, T* xf, hipStream_t s);
 
 // Level-0 solve: x = A0^{-1} b on the (2k-1)^dim interior nodes (float64);
 // batched over nsys systems zs apart, skipping those with active[z] == 0.
