@@ -436,10 +436,10 @@ void c0ip_problem::mg_level2d(int l, const T* b, T* x) {
     }
     check(c0ip::launch_apply2d<T, T>(k, Nl, w.coef, A, b, w.r.p, stream), "residual");
   }
-  check(c0ip::launch_restrict2d<T>(k, lv[l - 1]->N, w.ptab.p, w.r.p, wc.b.p, stream), "restrict");
+  check(c0ip::launch_restrict2d<T>(k, lv[l - 1]->N, w.r.p, wc.b.p, stream), "restrict");
   mg_level<T>(l - 1, wc.b.p, wc.x.p);
   if (post == 0) {
-    check(c0ip::launch_prolong2d<T>(k, lv[l - 1]->N, w.ptab.p, wc.x.p, A, x, stream), "prolong");
+    check(c0ip::launch_prolong2d<T>(k, lv[l - 1]->N, wc.x.p, A, x, stream), "prolong");
     return;
   }
   check(c0ip::launch_avs2d<T>(k, Nl, w.coef, w.eig, A, b, B, om, stream, 1, 0, nullptr, w.avs_variant, wc.x.p,
@@ -477,10 +477,10 @@ void c0ip_problem::mg_level(int l, const T* b, T* x) {
   }
   smooth<T>(l, b, x, mg.pre_steps, true);
   check(c0ip::launch_apply<T, T>(dim, k, lv[l]->N, w.coef, x, b, w.r.p, stream), "residual");
-  check(c0ip::launch_restrict<T>(dim, k, lv[l - 1]->N, w.ptab.p, w.r.p, wc.b.p, stream), "restrict");
+  check(c0ip::launch_restrict<T>(dim, k, lv[l - 1]->N, w.r.p, wc.b.p, stream), "restrict");
   mg_level<T>(l - 1, wc.b.p, wc.x.p);
   {
-    check(c0ip::launch_prolong_add<T>(dim, k, lv[l - 1]->N, w.ptab.p, wc.x.p, x, stream), "prolong");
+    check(c0ip::launch_prolong_add<T>(dim, k, lv[l - 1]->N, wc.x.p, x, stream), "prolong");
     smooth<T>(l, b, x, mg.post_steps, false);
   }
 }

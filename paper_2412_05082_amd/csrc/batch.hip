@@ -583,7 +583,7 @@ void c0ip_batch::vcycle(Group& g, hipStream_t gs) {
       }
     }
     hchk(launch_apply2d<T, T>(k, Nl, coef, A, b, r, gs, nA, nl, mask), "residual");
-    hchk(launch_restrict2d<T>(k, Nl / 2, c0ip_internal_ptab<T>(g.proto, l), r, lvbuf<T>(g, 1, l - 1).p, gs, nA, nl,
+    hchk(launch_restrict2d<T>(k, Nl / 2, r, lvbuf<T>(g, 1, l - 1).p, gs, nA, nl,
                               n1(l - 1), mask),
          "restrict");
   }
@@ -620,7 +620,7 @@ void c0ip_batch::vcycle(Group& g, hipStream_t gs) {
     T* A = (post % 2 == 1) ? lvbuf<T>(g, 3, l).p : x;
     T* B = (A == x) ? lvbuf<T>(g, 3, l).p : x;
     if (post == 0) {
-      hchk(launch_prolong2d<T>(k, Nl / 2, ptab, lvbuf<T>(g, 0, l - 1).p, A, x, gs, nA, n1(l - 1), nl, mask), "prolong");
+      hchk(launch_prolong2d<T>(k, Nl / 2, lvbuf<T>(g, 0, l - 1).p, A, x, gs, nA, n1(l - 1), nl, mask), "prolong");
       continue;
     }
     // first post-smoothing step from A + P e (fused), then alternate; ends in x

@@ -37,12 +37,12 @@ template <typename T>
 hipError_t launch_patch_smooth(int dim, int k, int N, const LevelEig<T>& e, const T* r, const T* x_in,
                                T* x_out, T omega, hipStream_t s);
 
-// Grid transfers (tensor-product 1D embedding, table [2][k][k+1]; 3D uses
-// the same table's compile-time form): bc = P^T rf; xf += P ec.
+// Grid transfers (tensor-product 1D embedding, compile-time table): bc = P^T rf;
+// xf += P ec.
 template <typename T>
-hipError_t launch_restrict(int dim, int k, int Nc, const T* table, const T* rf, T* bc, hipStream_t s);
+hipError_t launch_restrict(int dim, int k, int Nc, const T* rf, T* bc, hipStream_t s);
 template <typename T>
-hipError_t launch_prolong_add(int dim, int k, int Nc, const T* table, const T* ec, T* xf, hipStream_t s);
+hipError_t launch_prolong_add(int dim, int k, int Nc, const T* ec, T* xf, hipStream_t s);
 template <typename T>
 hipError_t launch_restrict3d(int k, int Nc, const T* rf, T* bc, hipStream_t s);
 template <typename T>
@@ -154,11 +154,11 @@ template <typename T>
 hipError_t launch_pre2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b, T* x1, T* r, T omega,
                         hipStream_t s);
 template <typename T>
-hipError_t launch_restrict2d(int k, int Nc, const T* table, const T* rf, T* bc, hipStream_t s, int nsys = 1,
+hipError_t launch_restrict2d(int k, int Nc, const T* rf, T* bc, hipStream_t s, int nsys = 1,
                              int64_t zf = 0, int64_t zc = 0, const int* active = nullptr);
 // xf = xin + P ec (xin may equal xf)
 template <typename T>
-hipError_t launch_prolong2d(int k, int Nc, const T* table, const T* ec, const T* xin, T* xf, hipStream_t s,
+hipError_t launch_prolong2d(int k, int Nc, const T* ec, const T* xin, T* xf, hipStream_t s,
                             int nsys = 1, int64_t zc = 0, int64_t zf = 0, const int* active = nullptr);
 template <typename Tin, typename T>
 hipError_t launch_apply3d(int k, int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* y, hipStream_t s);

@@ -12,6 +12,7 @@
 #include "exact.h"
 #include "kernels.h"
 #include "mvs2d.h"
+#include "tile2d.h"
 #include "tiles.h"
 
 namespace c0ip {
@@ -485,158 +486,118 @@ hipError_t mvs2d_colour_k(int N, int colour, const LevelCoef<T>& cf, const T* Q,
 }
 
 // ------------------------------------------------------------------ transfers
-// Restriction b_c = P^T r_f and prolongation x_f += P e_c in one launch each:
-// a workgroup owns TCC x TCC coarse cells, stages its fine (or coarse)
-// window in LDS and applies the 1D embedding table along x, then along y.
-// Table T[s][p][a]: value of coarse-cell basis a at the fine node of
-// position p in fine cell 2cc+s.
+// Restriction b_c = P^T r_f and prolongation x_f = x_in + P e_c in one launch
+// each, with the embedding table as compile-time constants (the same for every
+// penalty).  A workgroup owns TCX x TCY coarse cells; the first pass reads
+// memory straight into registers (y for the restriction, x for the
+// prolongation), the other one goes through LDS: one barrier, and no table to
+// wait for.  Bound by latency below the finest levels.  Restriction with the
+// table and both passes in LDS, against now, us: Q3 512^2 float32 7.8 and 5.5,
+// 128^2 4.7 and 2.6, Q4 64^2 float64 6.3 and 4.2.
 
-template <int K> struct TransferTile2D { static constexpr int TCC = K <= 4 ? 8 : 4; };
+template <int K> struct TransferTile2D { static constexpr int TCX = K <= 4 ? 8 : 4, TCY = K <= 3 ? 4 : 2; };
 
-template <typename T, int K, int TCC>
+template <typename T, int K>
 __global__ __launch_bounds__(kThreads) void restrict2d_kernel(const T* __restrict__ rf, T* __restrict__ bc, int Nc,
-                                                              const T* __restrict__ tab, int64_t zf, int64_t zc,
-                                                              const int* __restrict__ active) {
-  constexpr int CT = TCC * K, F = 2 * K * (TCC + 1), NT = 2 * K * (K + 1);
+                                                              int64_t zf, int64_t zc, const int* __restrict__ active) {
+  constexpr int TCX = TransferTile2D<K>::TCX, TCY = TransferTile2D<K>::TCY, S = 2 * K * (TCX + 1), SP = S | 1;
   if (active && !active[blockIdx.z]) return;
   rf += blockIdx.z * zf;
   bc += blockIdx.z * zc;
-  constexpr int NL = (F * F + kThreads - 1) / kThreads;
-  __shared__ T sF[F * F];
-  __shared__ T sT[F * CT];
-  __shared__ T sTb[NT];
+  __shared__ T sT[TCY * K * SP];
   const int nf = 2 * K * Nc + 1, nc = K * Nc + 1;
-  const int c0x = blockIdx.x * TCC, c0y = blockIdx.y * TCC;
-  const int fx0 = 2 * K * (c0x - 1), fy0 = 2 * K * (c0y - 1);
-  {
-    T v[NL];
+  const int cx0 = blockIdx.x * TCX, cy0 = blockIdx.y * TCY;
+  const tile2::Rows<T> buf(rf, nf, max(2 * K * (cy0 - 1), 0), min(2 * K * (cy0 + TCY), nf) - 1);
+  for (int it = threadIdx.x; it < S * TCY; it += kThreads) {
+    const int c = it / S, i = it - c * S, gx = 2 * K * (cx0 - 1) + i;
+    const bool on = gx >= 0 && gx < nf;
+    const unsigned o = buf.off(2 * K * (cy0 + c - 1), gx), step = (unsigned)(nf * (int)sizeof(T));
+    T in[4 * K], v[K];
 #pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      const int rr = e / F, cc = e - rr * F;
-      const int gy = fy0 + rr, gx = fx0 + cc;
-      v[q] = (e < F * F && gy >= 0 && gy < nf && gx >= 0 && gx < nf) ? rf[(size_t)gy * nf + gx] : T(0);
-    }
-    for (int e = threadIdx.x; e < NT; e += kThreads) sTb[e] = tab[e];
+    for (int q = 0; q < 4 * K; ++q) in[q] = buf.load(on ? o + q * step : tile2::kOff);
+    tile2::gather<T, K>(in, v);
 #pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      if (e < F * F) sF[e] = v[q];
-    }
+    for (int a = 0; a < K; ++a) sT[(c * K + a) * SP + i] = v[a];
   }
   __syncthreads();
-  for (int it = threadIdx.x; it < F * CT; it += kThreads) {
-    const int rr = it / CT, l = it - rr * CT;
-    const int I = c0x * K + l, cl = l / K, a = l - cl * K;  // coarse cell c0x+cl, position a
-    const T* row = sF + rr * F + 2 * K * (cl + 1);
-    T v = 0;
+  for (int it = threadIdx.x; it < TCY * K * TCX; it += kThreads) {
+    const int row = it / TCX, l = it - row * TCX, J = cy0 * K + row, I = (cx0 + l) * K;
+    if (cx0 + l >= Nc || J >= nc - 1) continue;
+    T in[4 * K], v[K];
 #pragma unroll
-    for (int q = 0; q < 2 * K; ++q) v += sTb[q * (K + 1) + a] * row[q];
-    if (a == 0) {
+    for (int q = 0; q < 4 * K; ++q) in[q] = sT[row * SP + 2 * K * l + q];
+    tile2::gather<T, K>(in, v);
 #pragma unroll
-      for (int q = 0; q < 2 * K; ++q) v += sTb[q * (K + 1) + K] * row[q - 2 * K];
-    }
-    sT[it] = (I > 0 && I < nc - 1) ? v : T(0);
+    for (int a = 0; a < K; ++a) bc[(size_t)J * nc + I + a] = J > 0 && I + a > 0 ? v[a] : T(0);
+    if (cx0 + l == Nc - 1) bc[(size_t)J * nc + nc - 1] = T(0);
   }
-  __syncthreads();
-  for (int it = threadIdx.x; it < CT * CT; it += kThreads) {
-    const int m = it / CT, l = it - m * CT;
-    const int I = c0x * K + l, J = c0y * K + m;
-    if (I >= nc || J >= nc) continue;
-    const int cm = m / K, a = m - cm * K;
-    const T* col = sT + (2 * K * (cm + 1)) * CT + l;
-    T v = 0;
-#pragma unroll
-    for (int q = 0; q < 2 * K; ++q) v += sTb[q * (K + 1) + a] * col[q * CT];
-    if (a == 0) {
-#pragma unroll
-      for (int q = 0; q < 2 * K; ++q) v += sTb[q * (K + 1) + K] * col[(q - 2 * K) * CT];
-    }
-    bc[(size_t)J * nc + I] = (J > 0 && J < nc - 1) ? v : T(0);
-  }
+  if (cy0 + TCY >= Nc)  // the last row
+    for (int l = threadIdx.x; l <= TCX * K; l += kThreads)
+      if (cx0 * K + l < nc) bc[(size_t)(nc - 1) * nc + cx0 * K + l] = T(0);
 }
 
-template <typename T, int K, int TCC>
+template <typename T, int K>
 __global__ __launch_bounds__(kThreads) void prolong2d_kernel(const T* __restrict__ ec, const T* xin, T* xf, int Nc,
-                                                             const T* __restrict__ tab, int64_t zc, int64_t zf,
-                                                             const int* __restrict__ active) {
-  constexpr int CW = TCC * K + 1, FT = 2 * K * TCC, NT = 2 * K * (K + 1);
+                                                             int64_t zc, int64_t zf, const int* __restrict__ active) {
+  constexpr int TCX = TransferTile2D<K>::TCX, TCY = TransferTile2D<K>::TCY, CW = TCY * K + 1, FT = 2 * K * TCX,
+                FP = FT | 1;
   if (active && !active[blockIdx.z]) return;
   ec += blockIdx.z * zc;
   xf += blockIdx.z * zf;
   xin += blockIdx.z * zf;
-  constexpr int NL = (CW * CW + kThreads - 1) / kThreads;
-  __shared__ T sC[CW * CW];
-  __shared__ T sT[CW * FT];
-  __shared__ T sTb[NT];
+  __shared__ T sT[CW * FP];
   const int nf = 2 * K * Nc + 1, nc = K * Nc + 1;
-  const int c0x = blockIdx.x * TCC, c0y = blockIdx.y * TCC;
-  {
-    T v[NL];
+  const int cx0 = blockIdx.x * TCX, cy0 = blockIdx.y * TCY;
+  const tile2::Rows<T> buf(ec, nc, cy0 * K, min((cy0 + TCY) * K, nc - 1));
+  for (int it = threadIdx.x; it < CW * TCX; it += kThreads) {
+    const int row = it / TCX, c = it - row * TCX;
+    const unsigned o = buf.off(cy0 * K + row, (cx0 + c) * K);
+    T in[K + 1], v[2 * K];
 #pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      const int rr = e / CW, cc = e - rr * CW;
-      const int gy = c0y * K + rr, gx = c0x * K + cc;
-      v[q] = (e < CW * CW && gy < nc && gx < nc) ? ec[(size_t)gy * nc + gx] : T(0);
-    }
-    for (int e = threadIdx.x; e < NT; e += kThreads) sTb[e] = tab[e];
+    for (int a = 0; a <= K; ++a) in[a] = buf.load(cx0 + c < Nc ? o + a * (unsigned)sizeof(T) : tile2::kOff);
+    tile2::spread<T, K>(in, v);
 #pragma unroll
-    for (int q = 0; q < NL; ++q) {
-      const int e = threadIdx.x + q * kThreads;
-      if (e < CW * CW) sC[e] = v[q];
-    }
+    for (int q = 0; q < 2 * K; ++q) sT[row * FP + 2 * K * c + q] = v[q];
   }
   __syncthreads();
-  for (int it = threadIdx.x; it < CW * FT; it += kThreads) {
-    const int rr = it / FT, l = it - rr * FT;
-    const int cf = l / K, p = l - cf * K, cl = cf >> 1, s2 = cf & 1;  // local coarse cell cl
-    const T* tb = sTb + (s2 * K + p) * (K + 1);
-    const T* src = sC + rr * CW + cl * K;
-    T v = 0;
+  // fine nodes of the tile's cells; the last cells also own the mesh's last (boundary) row and column
+  for (int it = threadIdx.x; it < FT * TCY; it += kThreads) {
+    const int c = it / FT, l = it - c * FT, gx = 2 * K * cx0 + l, gy = 2 * K * (cy0 + c);
+    if (gx >= nf - 1 || cy0 + c >= Nc) continue;
+    T in[K + 1], v[2 * K], x[2 * K];
 #pragma unroll
-    for (int a = 0; a <= K; ++a) v += tb[a] * src[a];
-    sT[it] = v;
-  }
-  __syncthreads();
-  // fine nodes [2k c0, 2k (c0 + TCC)) of this tile, plus the last (boundary)
-  // node of the mesh for the last tile, so that every output is written
-  constexpr int FO = FT + 1;
-  for (int it = threadIdx.x; it < FO * FO; it += kThreads) {
-    const int m = it / FO, l = it - m * FO;
-    const int fx = 2 * K * c0x + l, fy = 2 * K * c0y + m;
-    if (fx >= nf || fy >= nf) continue;
-    if ((l == FT && fx != nf - 1) || (m == FT && fy != nf - 1)) continue;
-    const size_t idx = (size_t)fy * nf + fx;
-    if (fx == 0 || fy == 0 || fx == nf - 1 || fy == nf - 1) {
-      xf[idx] = T(0);
-      continue;
+    for (int q = 0; q < 2 * K; ++q) x[q] = xin[(size_t)(gy + q) * nf + gx];
+#pragma unroll
+    for (int a = 0; a <= K; ++a) in[a] = sT[(c * K + a) * FP + l];
+    tile2::spread<T, K>(in, v);
+#pragma unroll
+    for (int q = 0; q < 2 * K; ++q) {
+      T* p = xf + (size_t)(gy + q) * nf + gx;
+      *p = gx > 0 && gy + q > 0 ? x[q] + v[q] : T(0);
+      if (gx == nf - 2) p[1] = T(0);
     }
-    const int cf = m / K, p = m - cf * K, cl = cf >> 1, s2 = cf & 1;
-    const T* tb = sTb + (s2 * K + p) * (K + 1);
-    const T* src = sT + (cl * K) * FT + l;
-    T v = 0;
-#pragma unroll
-    for (int a = 0; a <= K; ++a) v += tb[a] * src[a * FT];
-    xf[idx] = xin[idx] + v;
+    if (cy0 + c == Nc - 1) {
+      xf[(size_t)(nf - 1) * nf + gx] = T(0);
+      if (gx == nf - 2) xf[(size_t)nf * nf - 1] = T(0);
+    }
   }
 }
 
 template <typename T, int K>
-hipError_t restrict2d_k(int Nc, const T* tab, const T* rf, T* bc, hipStream_t s, int nsys, int64_t zf,
-                        int64_t zc, const int* active) {
-  constexpr int TCC = TransferTile2D<K>::TCC;
-  const int nt = (Nc + TCC - 1) / TCC;
-  restrict2d_kernel<T, K, TCC><<<dim3(nt, nt, nsys), kThreads, 0, s>>>(rf, bc, Nc, tab, zf, zc, active);
+hipError_t restrict2d_k(int Nc, const T* rf, T* bc, hipStream_t s, int nsys, int64_t zf, int64_t zc,
+                        const int* active) {
+  using G = TransferTile2D<K>;
+  restrict2d_kernel<T, K><<<dim3((Nc + G::TCX - 1) / G::TCX, (Nc + G::TCY - 1) / G::TCY, nsys), kThreads, 0, s>>>(
+      rf, bc, Nc, zf, zc, active);
   return hipGetLastError();
 }
 
 template <typename T, int K>
-hipError_t prolong2d_k(int Nc, const T* tab, const T* ec, const T* xin, T* xf, hipStream_t s, int nsys,
-                       int64_t zc, int64_t zf, const int* active) {
-  constexpr int TCC = TransferTile2D<K>::TCC;
-  const int nt = (Nc + TCC - 1) / TCC;
-  prolong2d_kernel<T, K, TCC><<<dim3(nt, nt, nsys), kThreads, 0, s>>>(ec, xin, xf, Nc, tab, zc, zf, active);
+hipError_t prolong2d_k(int Nc, const T* ec, const T* xin, T* xf, hipStream_t s, int nsys, int64_t zc, int64_t zf,
+                       const int* active) {
+  using G = TransferTile2D<K>;
+  prolong2d_kernel<T, K><<<dim3((Nc + G::TCX - 1) / G::TCX, (Nc + G::TCY - 1) / G::TCY, nsys), kThreads, 0, s>>>(
+      ec, xin, xf, Nc, zc, zf, active);
   return hipGetLastError();
 }
 
@@ -676,28 +637,28 @@ hipError_t launch_mvs2d_colour_exact(int k, int N, int colour, const LevelCoef<T
 }
 
 template <typename T>
-hipError_t launch_restrict2d(int k, int Nc, const T* table, const T* rf, T* bc, hipStream_t s, int nsys,
+hipError_t launch_restrict2d(int k, int Nc, const T* rf, T* bc, hipStream_t s, int nsys,
                              int64_t zf, int64_t zc, const int* active) {
-#define CALL(K) restrict2d_k<T, K>(Nc, table, rf, bc, s, nsys, zf, zc, active)
+#define CALL(K) restrict2d_k<T, K>(Nc, rf, bc, s, nsys, zf, zc, active)
   C0IP_DISPATCH_K(k, CALL)
 #undef CALL
 }
 
 template <typename T>
-hipError_t launch_prolong2d(int k, int Nc, const T* table, const T* ec, const T* xin, T* xf, hipStream_t s,
+hipError_t launch_prolong2d(int k, int Nc, const T* ec, const T* xin, T* xf, hipStream_t s,
                             int nsys, int64_t zc, int64_t zf, const int* active) {
-#define CALL(K) prolong2d_k<T, K>(Nc, table, ec, xin, xf, s, nsys, zc, zf, active)
+#define CALL(K) prolong2d_k<T, K>(Nc, ec, xin, xf, s, nsys, zc, zf, active)
   C0IP_DISPATCH_K(k, CALL)
 #undef CALL
 }
 
-template hipError_t launch_restrict2d<double>(int, int, const double*, const double*, double*, hipStream_t, int,
+template hipError_t launch_restrict2d<double>(int, int, const double*, double*, hipStream_t, int,
                                               int64_t, int64_t, const int*);
-template hipError_t launch_restrict2d<float>(int, int, const float*, const float*, float*, hipStream_t, int, int64_t,
+template hipError_t launch_restrict2d<float>(int, int, const float*, float*, hipStream_t, int, int64_t,
                                              int64_t, const int*);
-template hipError_t launch_prolong2d<double>(int, int, const double*, const double*, const double*, double*,
+template hipError_t launch_prolong2d<double>(int, int, const double*, const double*, double*,
                                              hipStream_t, int, int64_t, int64_t, const int*);
-template hipError_t launch_prolong2d<float>(int, int, const float*, const float*, const float*, float*, hipStream_t,
+template hipError_t launch_prolong2d<float>(int, int, const float*, const float*, float*, hipStream_t,
                                             int, int64_t, int64_t, const int*);
 template hipError_t launch_patch2d_atomic<double>(int, int, const LevelEig<double>&, const double*, double*,
                                                   double, hipStream_t);

@@ -345,13 +345,13 @@ hipError_t launch_patch_smooth(int dim, int k, int N, const LevelEig<T>& e, cons
 }
 
 template <typename T>
-hipError_t launch_restrict(int dim, int k, int Nc, const T* table, const T* rf, T* bc, hipStream_t s) {
-  return dim == 2 ? launch_restrict2d<T>(k, Nc, table, rf, bc, s) : launch_restrict3d<T>(k, Nc, rf, bc, s);
+hipError_t launch_restrict(int dim, int k, int Nc, const T* rf, T* bc, hipStream_t s) {
+  return dim == 2 ? launch_restrict2d<T>(k, Nc, rf, bc, s) : launch_restrict3d<T>(k, Nc, rf, bc, s);
 }
 
 template <typename T>
-hipError_t launch_prolong_add(int dim, int k, int Nc, const T* table, const T* ec, T* xf, hipStream_t s) {
-  return dim == 2 ? launch_prolong2d<T>(k, Nc, table, ec, xf, xf, s) : launch_prolong3d<T>(k, Nc, ec, xf, s);
+hipError_t launch_prolong_add(int dim, int k, int Nc, const T* ec, T* xf, hipStream_t s) {
+  return dim == 2 ? launch_prolong2d<T>(k, Nc, ec, xf, xf, s) : launch_prolong3d<T>(k, Nc, ec, xf, s);
 }
 
 template <typename T, int DIM, int K>
@@ -452,10 +452,10 @@ template hipError_t launch_patch_smooth<double>(int, int, int, const LevelEig<do
                                                 const double*, double*, double, hipStream_t);
 template hipError_t launch_patch_smooth<float>(int, int, int, const LevelEig<float>&, const float*, const float*,
                                                float*, float, hipStream_t);
-template hipError_t launch_restrict<double>(int, int, int, const double*, const double*, double*, hipStream_t);
-template hipError_t launch_restrict<float>(int, int, int, const float*, const float*, float*, hipStream_t);
-template hipError_t launch_prolong_add<double>(int, int, int, const double*, const double*, double*, hipStream_t);
-template hipError_t launch_prolong_add<float>(int, int, int, const float*, const float*, float*, hipStream_t);
+template hipError_t launch_restrict<double>(int, int, int, const double*, double*, hipStream_t);
+template hipError_t launch_restrict<float>(int, int, int, const float*, float*, hipStream_t);
+template hipError_t launch_prolong_add<double>(int, int, int, const double*, double*, hipStream_t);
+template hipError_t launch_prolong_add<float>(int, int, int, const float*, float*, hipStream_t);
 template hipError_t launch_coarse<double>(int, int, const double*, const double*, double*, hipStream_t, int, int64_t,
                                           const int*);
 template hipError_t launch_coarse<float>(int, int, const double*, const float*, float*, hipStream_t, int, int64_t,

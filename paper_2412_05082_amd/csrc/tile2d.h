@@ -384,5 +384,35 @@ struct Prolong {
   }
 };
 
+// Transfers, with the compile-time embedding table pt[s][p][a] (value of coarse
+// basis a at the fine node of position p in fine cell s of the coarse cell).
+// The k coarse values of a cell from the fine nodes of its left neighbour and its own (in[0..4k-1]).
+template <typename T, int K>
+__device__ __forceinline__ void gather(const T* in, T (&o)[K]) {
+#pragma unroll
+  for (int a = 0; a < K; ++a) {
+    T v = 0;
+#pragma unroll
+    for (int q = 0; q < 2 * K; ++q) v = mad((T)RefCoef<K>::pt[q / K][q % K][a], in[2 * K + q], v);
+    if (a == 0) {
+#pragma unroll
+      for (int q = 0; q < 2 * K; ++q) v = mad((T)RefCoef<K>::pt[q / K][q % K][K], in[q], v);
+    }
+    o[a] = v;
+  }
+}
+
+// The 2k fine values of a coarse cell from its k + 1 nodes.
+template <typename T, int K>
+__device__ __forceinline__ void spread(const T* in, T (&o)[2 * K]) {
+#pragma unroll
+  for (int q = 0; q < 2 * K; ++q) {
+    T v = 0;
+#pragma unroll
+    for (int a = 0; a <= K; ++a) v = mad((T)RefCoef<K>::pt[q / K][q % K][a], in[a], v);
+    o[q] = v;
+  }
+}
+
 }  // namespace tile2
 }  // namespace c0ip

@@ -3,12 +3,11 @@
 // position p in fine cell s of the coarse cell): restriction b_c = P^T r_f and
 // prolongation x_f += P e_c.  A workgroup owns TC x TC coarse cells of one
 // layer; a z pass per column straight from memory, then an x pass and a y pass
-// in LDS.  (One launch per axis with both intermediate results in memory took
-// 66 us to restrict and 53 to prolong at Q2 128^3 float32 (27 and 25 now), and 14 on small
-// meshes (under 5).)
+// in LDS.  One launch per axis with both intermediate results in memory took
+// 66 us to restrict and 53 to prolong at Q2 128^3 float32, against 27 and 25
+// now, and 14 on small meshes, against 5.
 #include "faces3d.h"
 #include "kernels.h"
-#include "refband.h"
 #include "tile2d.h"
 
 namespace c0ip {
@@ -18,34 +17,6 @@ constexpr int kNth = 256;
 
 // Coarse cells per axis of a workgroup's tile, as LDS allows.
 template <int K> struct TransferTile { static constexpr int TC = K <= 3 ? 4 : K <= 5 ? 2 : 1; };
-
-// The k coarse values of a cell from the fine nodes of its left neighbour and its own (in[0..4k-1]).
-template <typename T, int K>
-__device__ __forceinline__ void gather(const T* in, T (&o)[K]) {
-#pragma unroll
-  for (int a = 0; a < K; ++a) {
-    T v = 0;
-#pragma unroll
-    for (int q = 0; q < 2 * K; ++q) v = ref::mad((T)RefCoef<K>::pt[q / K][q % K][a], in[2 * K + q], v);
-    if (a == 0) {
-#pragma unroll
-      for (int q = 0; q < 2 * K; ++q) v = ref::mad((T)RefCoef<K>::pt[q / K][q % K][K], in[q], v);
-    }
-    o[a] = v;
-  }
-}
-
-// The 2k fine values of a coarse cell from its k + 1 nodes.
-template <typename T, int K>
-__device__ __forceinline__ void spread(const T* in, T (&o)[2 * K]) {
-#pragma unroll
-  for (int q = 0; q < 2 * K; ++q) {
-    T v = 0;
-#pragma unroll
-    for (int a = 0; a <= K; ++a) v = ref::mad((T)RefCoef<K>::pt[q / K][q % K][a], in[a], v);
-    o[q] = v;
-  }
-}
 
 template <typename T, int K>
 __global__ __launch_bounds__(kNth) void restrict3d_kernel(const T* __restrict__ rf, T* __restrict__ bc, int Nc,
@@ -69,7 +40,7 @@ __global__ __launch_bounds__(kNth) void restrict3d_kernel(const T* __restrict__ 
     T in[4 * K], o[K];
 #pragma unroll
     for (int z = 0; z < 4 * K; ++z) in[z] = z >= 2 * K || cz > 0 ? p[(int64_t)(z - 2 * K) * (int64_t)pl] : T(0);
-    gather<T, K>(in, o);
+    tile2::gather<T, K>(in, o);
 #pragma unroll
     for (int a = 0; a < K; ++a) sF[(a * S + j) * SP + i] = on ? o[a] : T(0);
   }
@@ -79,7 +50,7 @@ __global__ __launch_bounds__(kNth) void restrict3d_kernel(const T* __restrict__ 
     T in[4 * K], o[K];
 #pragma unroll
     for (int i = 0; i < 4 * K; ++i) in[i] = sF[row * SP + 2 * K * c + i];
-    gather<T, K>(in, o);
+    tile2::gather<T, K>(in, o);
 #pragma unroll
     for (int a = 0; a < K; ++a) sT[row * TXP + c * K + a] = o[a];
   }
@@ -91,7 +62,7 @@ __global__ __launch_bounds__(kNth) void restrict3d_kernel(const T* __restrict__ 
     T in[4 * K], o[K];
 #pragma unroll
     for (int i = 0; i < 4 * K; ++i) in[i] = sT[(a0 * S + 2 * K * c + i) * TXP + l];
-    gather<T, K>(in, o);
+    tile2::gather<T, K>(in, o);
 #pragma unroll
     for (int a = 0; a < K; ++a)
       bc[((size_t)gz * nc + gy + a) * nc + gx] = gx > 0 && gy + a > 0 && gz > 0 ? o[a] : T(0);
@@ -116,7 +87,7 @@ __global__ __launch_bounds__(kNth) void prolong3d_kernel(const T* __restrict__ e
     T in[K + 1], o[2 * K];
 #pragma unroll
     for (int a = 0; a <= K; ++a) in[a] = p[a * pl];
-    spread<T, K>(in, o);
+    tile2::spread<T, K>(in, o);
 #pragma unroll
     for (int z = 0; z < 2 * K; ++z) sC[(z * CW + j) * CP + i] = on ? o[z] : T(0);
   }
@@ -126,7 +97,7 @@ __global__ __launch_bounds__(kNth) void prolong3d_kernel(const T* __restrict__ e
     T in[K + 1], o[2 * K];
 #pragma unroll
     for (int a = 0; a <= K; ++a) in[a] = sC[row * CP + c * K + a];
-    spread<T, K>(in, o);
+    tile2::spread<T, K>(in, o);
 #pragma unroll
     for (int i = 0; i < 2 * K; ++i) sT[row * FP + 2 * K * c + i] = o[i];
   }
@@ -138,7 +109,7 @@ __global__ __launch_bounds__(kNth) void prolong3d_kernel(const T* __restrict__ e
     T in[K + 1], o[2 * K];
 #pragma unroll
     for (int a = 0; a <= K; ++a) in[a] = sT[(z * CW + c * K + a) * FP + l];
-    spread<T, K>(in, o);
+    tile2::spread<T, K>(in, o);
     T* x = xf + ((size_t)gz * nf + gy) * nf + gx;
     T v[2 * K];
 #pragma unroll
