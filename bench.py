@@ -87,7 +87,7 @@ def parse():
 # HBM traffic of the fused smoother, from the committed counter summary: one
 # row per tile variant, valid only for the kernel source it was measured on.
 COUNTERS = os.path.join(ROOT, "profiles", "avs2d_f32_2d_q3_512_counters.md")
-KERNEL_SRC = os.path.join(ROOT, "paper_2412_05082_amd", "csrc", "op2d_impl.h")
+KERNEL_SRC = os.path.join(ROOT, "paper_2412_05082_amd", "csrc", "smooth2d_impl.h")
 
 
 def measured_traffic(variant):
@@ -660,7 +660,7 @@ def main():
                                "f64": p64.tuned_variant(dtype=P.C0IP_F64)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": f"avs2d_kernel<float, k=3, tile variant {var32}>: fused float32 smoother step "
+                     "kernel": f"step2d_kernel<float, k=3, tile variant {var32}>: fused float32 smoother step "
                                f"S(x,b) (residual in LDS + patch solves), 12 B/DoF x {n} DoFs per launch; "
                                f"traffic = HBM bytes per launch from FETCH_SIZE/WRITE_SIZE"},
     }
