@@ -31,6 +31,7 @@
 namespace c0ip {
 namespace {
 
+using tile2::scalar;
 using tile::variant;
 
 template <int K> struct PatchBoxThreads;  // a y line per thread, whole waves
@@ -45,15 +46,6 @@ struct PatchBox {
   static constexpr int MP = M | 1;                                                // odd LDS row stride
   static_assert(TX * TX <= NTH && S <= M, "an owned column per thread; rows hold nodes and modes");
 };
-
-// Offset of a basis as a scalar.  The empty statement keeps the loads of a
-// basis from being shared between two uses: all of it would not fit the
-// registers.
-__device__ __forceinline__ int scalar(int v) {
-  v = __builtin_amdgcn_readfirstlane(v);
-  asm volatile("" : "+s"(v));
-  return v;
-}
 
 template <typename T, int K, int NTH>
 __global__ __launch_bounds__(NTH) void patch3d_box_kernel(const T* __restrict__ r, const T* xin, T* xout, int N,

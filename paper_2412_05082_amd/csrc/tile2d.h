@@ -230,15 +230,55 @@ struct StageEig {
   }
 };
 
+// Offset of a basis as a scalar.  The empty statement keeps the loads of a
+// basis from being shared between two uses: all of it would not fit the
+// registers of a large one.
+__device__ __forceinline__ int scalar(int v) {
+  v = __builtin_amdgcn_readfirstlane(v);
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+// A basis (n x n values at offset o) for one more use.  From 256 registers on
+// (k = 7 in float64) it is loaded again for every transform, a row at a time:
+// S(x, b) Q7 256^2 469 -> 244 us, 64^2 31 -> 18.  Smaller ones are faster when
+// the compiler keeps what it can (Q6 256^2 float64 183 against 204, Q7 256^2
+// float32 74 against 85).
+template <typename T, int n>
+constexpr bool kBigBasis = n * n * (int)sizeof(T) / 4 > 256;
+template <typename T, int n, bool INT>
+__device__ __forceinline__ const T* basis(const T* q, int o) {
+  if constexpr (kBigBasis<T, n>) {
+    if constexpr (INT)
+      o = scalar(o);
+    else
+      asm volatile("" : "+v"(o));
+  }
+  return q + o;
+}
+
+
 // One 1D transform: out[c] = sum_a Q[a][c] in[a] (FWD) or out[a] = sum_c Q[a][c] in[c].
 template <typename T, int n, bool FWD>
 __device__ __forceinline__ void tr1(const T* __restrict__ q, const T (&in)[n], T (&out)[n]) {
+  if constexpr (FWD && kBigBasis<T, n>) {  // row after row of Q, like the other direction
 #pragma unroll
-  for (int i = 0; i < n; ++i) {
-    T s = (FWD ? q[i] : q[i * n]) * in[0];
+    for (int i = 0; i < n; ++i) out[i] = q[i] * in[0];
 #pragma unroll
-    for (int j = 1; j < n; ++j) s = mad(FWD ? q[j * n + i] : q[i * n + j], in[j], s);
-    out[i] = s;
+    for (int j = 1; j < n; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < n; ++i) out[i] = mad(q[j * n + i], in[j], out[i]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      if (kBigBasis<T, n>) __builtin_amdgcn_sched_barrier(0);
+      T s = (FWD ? q[i] : q[i * n]) * in[0];
+#pragma unroll
+      for (int j = 1; j < n; ++j) s = mad(FWD ? q[j * n + i] : q[i * n + j], in[j], s);
+      out[i] = s;
+    }
   }
 }
 
@@ -254,7 +294,7 @@ __device__ __forceinline__ void fd_x(const T* __restrict__ sR, int rp, T* __rest
     T in[n], out[n];
 #pragma unroll
     for (int a = 0; a < n; ++a) in[a] = sR[row * rp + px * S::K + a];
-    tr1<T, n, true>(INT ? q0 : sQ + tile::variant(cx0 + px, N) * S::NN, in, out);
+    tr1<T, n, true>(INT ? basis<T, n, true>(q0, 0) : basis<T, n, false>(sQ, tile::variant(cx0 + px, N) * S::NN), in, out);
 #pragma unroll
     for (int a = 0; a < n; ++a) sM[row * S::XP + px * n + a] = out[a];
   }
@@ -274,12 +314,13 @@ __device__ __forceinline__ void fd_y(const T* __restrict__ sM, T* __restrict__ s
     if (INT || (vx >= 1 && vx <= N - 1 && vy >= 1 && vy <= N - 1)) {
       const int ty = INT ? 0 : tile::variant(vy, N);
       const T lx = sLam[(INT ? 0 : tile::variant(vx, N)) * n + mx];
-      const T* q = INT ? q0 : sQ + ty * S::NN;
+      const T* q = INT ? basis<T, n, true>(q0, 0) : basis<T, n, false>(sQ, ty * S::NN);
 #pragma unroll
       for (int a = 0; a < n; ++a) in[a] = sM[(py * S::K + a) * S::XP + col];
       tr1<T, n, true>(q, in, w);
 #pragma unroll
       for (int m = 0; m < n; ++m) w[m] *= INT ? sD[m * n + mx] : T(1) / (lx + sLam[ty * n + m]);
+      if (kBigBasis<T, n>) q = INT ? basis<T, n, true>(q0, 0) : basis<T, n, false>(sQ, ty * S::NN);
       tr1<T, n, false>(q, w, in);
     } else {
 #pragma unroll
@@ -312,10 +353,11 @@ __device__ __forceinline__ void fd_out(const T* __restrict__ sU, T (&out)[S::K],
       wb[m] += ub[n + m];
     }
   }
-  const T* qa = INT ? q0 : sQ + tile::variant(cx0 + c, N) * S::NN;
-  const T* qb = INT ? q0 : sQ + tile::variant(cx0 + c + 1, N) * S::NN;
+  const T* qa = INT ? basis<T, n, true>(q0, 0) : basis<T, n, false>(sQ, tile::variant(cx0 + c, N) * S::NN);
+  const T* qb = INT ? basis<T, n, true>(q0, 0) : basis<T, n, false>(sQ, tile::variant(cx0 + c + 1, N) * S::NN);
 #pragma unroll
   for (int p = 0; p < K; ++p) {
+    if (kBigBasis<T, n>) __builtin_amdgcn_sched_barrier(0);
     T a = qa[(K - 1 + p) * n] * wa[0];
 #pragma unroll
     for (int m = 1; m < n; ++m) a = mad(qa[(K - 1 + p) * n + m], wa[m], a);
