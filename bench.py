@@ -85,9 +85,21 @@ def parse():
 
 
 # HBM traffic of the fused smoother, from the committed counter summary: one
-# row per tile variant, valid only for the kernel source it was measured on.
+# row per tile variant, valid only for the kernel source it was measured on:
+# every file the kernel is made of, in this order.
 COUNTERS = os.path.join(ROOT, "profiles", "avs2d_f32_2d_q3_512_counters.md")
-KERNEL_SRC = os.path.join(ROOT, "paper_2412_05082_amd", "csrc", "smooth2d_impl.h")
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2412_05082_amd", "csrc", f)
+               for f in ("smooth2d_impl.h", "tile2d.h", "refband.h", "tiles.h", "gen_refcoef.cpp")]
+
+
+def kernel_digest():
+    """sha256 of the fused smoother's sources one after the other."""
+    import hashlib
+    h = hashlib.sha256()
+    for path in KERNEL_SRCS:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic(variant):
@@ -95,11 +107,10 @@ def measured_traffic(variant):
     fused smoother step with this tile variant, or None when the summary is
     missing, has no row for it, or was taken on another version of the
     kernel source."""
-    import hashlib
     import re
     try:
         text = open(COUNTERS).read()
-        src = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()
+        src = kernel_digest()
     except OSError:
         return None
     m = re.search(r"kernel source sha256: ([0-9a-f]{64})", text)
