@@ -104,11 +104,13 @@ typedef struct {
  * mvs_residual: where a 2D multiplicative step forms each colour's
  *   residual b - A x.  1 = in the colour's own launch, on its patches'
  *   rows only (x staged in LDS around each patch); 2 = a full residual pass
- *   with the tiled operator before each colour's solves; 0 = automatic (1 on
- *   levels under 1.5 * 2^20 DoFs, where launches dominate, 2 on finer
- *   ones).  The modes form the same sums and agree to rounding.  Ignored
- *   in 3D (always 2) and by the additive smoother; batched solves take 0
- *   only.  Other values: C0IP_EINVAL. */
+ *   with the tiled operator before each colour's solves; 0 = automatic, the
+ *   faster of the two: 1 with the default penalty up to degree 6, otherwise
+ *   1 on levels under 1.5 * 2^20 DoFs and 2 on finer ones.  The modes form
+ *   the same sums and agree to rounding.  Ignored by the additive smoother
+ *   and in 3D, where the residual is formed in the colour's launch with the
+ *   default penalty up to degree 4 and by a full pass otherwise; batched
+ *   solves take 0 only.  Other values: C0IP_EINVAL. */
 typedef struct {
   double omega;
   int pre_steps, post_steps;
