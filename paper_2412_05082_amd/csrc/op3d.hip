@@ -28,9 +28,9 @@
 // constants (generated at build time by gen_refcoef.cpp); every term of the
 // 3D operator then carries the same factor 1/h, applied to the output.
 // Along x and y every tile uses these constants: boundary nodes are staged
-// as 0, which drops their columns, and the only other boundary rows, the k
-// rows of B next to either end (the point term at the boundary), are
-// corrected by the lanes that own those cells, from constants too.
+// as 0, which drops their columns, and in the only other boundary rows, the k
+// rows of B next to either end (the point term at the boundary), the lanes
+// that own those cells take other constants for the columns that differ.
 // Rows of boundary nodes are masked on the way out.  (Redoing every product
 // of the boundary tiles with per-lane rows from an LDS table took 441 us
 // for 30 % of the tiles of 3D Q3 128^3 in float64, against 337 us for the
@@ -71,32 +71,59 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// The boundary rows of B in a cheaper form than ref::boundary_b: a += the
-// difference of their coefficients from the periodic rows times the input, on
-// the k nodes of the boundary cell.  The whole rows reach three cells, for
-// which the window along z leaves no registers (Q3 128^3 float64 spills: 679
-// us against 418).  The difference rounds at the size of the larger
-// coefficient; for k <= 4 that does not show in the results (at k = 5 it
-// does).
+// Coefficient of B at column j (a cell's nodes count from 0) of the cell's row p, for rows whose boundary term is at
+// the lower end (E = 1), at the upper end (E = 2) or absent (E = 0).
+template <int K, int E>
+constexpr double edge_b(int p, int j) {
+  if (E == 1) return p > 0 ? RefCoef<K>::bl[p - 1][j - 1] : RefCoef<K>::bl[K - 1][K + j - 1];
+  if (E == 2) return RefCoef<K>::bl[K - 1 - p][K - 1 - j];
+  return RefCoef<K>::b[p][2 * K + j - p];
+}
+
+// a += the columns lo..hi of the cell's row p.
+template <typename T, int K, int E>
+__device__ __forceinline__ T edge_sum(T a, const T* v, int p, int lo, int hi) {
+#pragma unroll
+  for (int j = lo; j <= hi; ++j) a = ref::mad((T)edge_b<K, E>(p, j), v[j], a);
+  return a;
+}
+
+// The k rows of B of cell c: a[p] = row p times the input, v[j] = the input at the cell's node j.  The rows next to
+// either end differ from the periodic ones in the k coefficients of the boundary cell's nodes only (the point term
+// there), so a row is one sum, from its lowest column up, whose columns around its own cell take the coefficients
+// that hold there.  (Whole second products for those rows reach three cells, for which the window along z leaves no
+// registers: Q3 128^3 float64 spills, 679 us against 418.  The periodic product plus the difference of the
+// coefficients rounds at the size of the larger of the two, up to 2.1 times the error of a row at k = 4, and is no
+// faster: Q3 128^3 float64 429 us against 424 here, Q2 96 against 88.)  Meshes of at least three cells.
 template <typename T, int K>
-__device__ __forceinline__ void add_boundary_b(T (&a)[K], const T* v, int c, int N) {
-  static_assert(K <= 4, "rounding");
-  if (c == 0) {  // rows 1..k-1 here, row k with the next cell
+__device__ __forceinline__ void rows_b(T (&a)[K], const T* v, int c, int N) {
+  a[0] = (T)edge_b<K, 0>(0, -2 * K) * v[-2 * K];
+  a[0] = edge_sum<T, K, 0>(a[0], v, 0, 1 - 2 * K, -K);
 #pragma unroll
-    for (int p = 1; p < K; ++p)
-#pragma unroll
-      for (int j = 1; j <= K; ++j) a[p] += (T)RefCoef<K>::db[p - 1][j - 1] * v[j];
+  for (int p = 1; p < K; ++p) {
+    a[p] = (T)edge_b<K, 0>(p, -K) * v[-K];
+    a[p] = edge_sum<T, K, 0>(a[p], v, p, 1 - K, -1);
   }
-  if (c == 1) {
+  if (c > 1 && c < N - 1) {
+    a[0] = edge_sum<T, K, 0>(a[0], v, 0, 1 - K, K - 1);
 #pragma unroll
-    for (int j = 1; j <= K; ++j) a[0] += (T)RefCoef<K>::db[K - 1][j - 1] * v[j - K];
+    for (int p = 1; p < K; ++p) a[p] = edge_sum<T, K, 0>(a[p], v, p, 0, K);
+  } else if (c == N - 1) {  // node k is on the boundary, its value 0
+    a[0] = edge_sum<T, K, 0>(a[0], v, 0, 1 - K, -1);
+#pragma unroll
+    for (int p = 0; p < K; ++p) a[p] = edge_sum<T, K, 2>(a[p], v, p, 0, K - 1);
+  } else if (c == 1) {
+    a[0] = edge_sum<T, K, 1>(a[0], v, 0, 1 - K, 0);
+    a[0] = edge_sum<T, K, 0>(a[0], v, 0, 1, K - 1);
+#pragma unroll
+    for (int p = 1; p < K; ++p) a[p] = edge_sum<T, K, 0>(a[p], v, p, 0, K);
+  } else {  // the first cell: node 0 is on the boundary
+#pragma unroll
+    for (int p = 1; p < K; ++p) a[p] = edge_sum<T, K, 1>(a[p], v, p, 1, K);
   }
-  if (c == N - 1) {
+  a[0] = edge_sum<T, K, 0>(a[0], v, 0, K, 2 * K);
 #pragma unroll
-    for (int p = 0; p < K; ++p)
-#pragma unroll
-      for (int j = 0; j < K; ++j) a[p] += (T)RefCoef<K>::db[K - 1 - p][K - 1 - j] * v[j];
-  }
+  for (int p = 1; p < K; ++p) a[p] = edge_sum<T, K, 0>(a[p], v, p, K + 1, 2 * K);
 }
 
 // Tile geometry: TXC x TYC cells, x items of CW cells.  One thread per
@@ -133,9 +160,12 @@ __device__ __forceinline__ void xpass3(const T* __restrict__ sX, T* __restrict__
       for (int w = 0; w < CW; ++w) {
         const T* v = in + (w * K + H - LO);
         T a[K];
+        if constexpr (OP == 2) {
+          rows_b<T, K>(a, v, cx0 + g * CW + w, N);
+        } else {
 #pragma unroll
-        for (int p = 0; p < K; ++p) a[p] = band_ref<T, OP, K>(v + p, p);
-        if constexpr (OP == 2) add_boundary_b<T, K>(a, v, cx0 + g * CW + w, N);
+          for (int p = 0; p < K; ++p) a[p] = band_ref<T, OP, K>(v + p, p);
+        }
 #pragma unroll
         for (int p = 0; p < K; ++p) out[(g * CW + w) * K + p] = a[p];
       }
@@ -189,9 +219,8 @@ __device__ __forceinline__ void ypass3(const T* __restrict__ sTM, const T* __res
       const T* v = t + p + 2 * K;
       S2[p] = band_ref<T, 0, K>(v, p);
       S3[p] = T(2) * (S3[p] + band_ref<T, 1, K>(v, p));
-      sb[p] = band_ref<T, 2, K>(v, p);
     }
-    add_boundary_b<T, K>(sb, t + 2 * K, cy0 + cy, N);
+    rows_b<T, K>(sb, t + 2 * K, cy0 + cy, N);
 #pragma unroll
     for (int p = 0; p < K; ++p) S1[p] += sb[p];
   }
