@@ -417,7 +417,7 @@ void c0ip_problem::mg_level2d(int l, const T* b, T* x) {
   const T om = (T)mg.omega;
   T* A = (post % 2 == 1) ? w.t.p : x;
   T* B = (A == x) ? w.t.p : x;
-  const bool fused_pre = pre == 1 && w.coef.ref && Nl <= c0ip::pre2d_max_n(k, (int)sizeof(T));
+  const bool fused_pre = pre == 1 && Nl <= c0ip::pre2d_max_n(k, (int)sizeof(T), w.coef.ref != nullptr);
   if (fused_pre) {
     // x1 = S(0, b) and r = b - A x1 in one launch
     check(c0ip::launch_pre2d<T>(k, Nl, w.coef, w.eig, b, A, w.r.p, om, stream), "pre-smoother + residual");

@@ -142,17 +142,27 @@ template <typename T>
 hipError_t launch_step2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* x, const T* b, T* xout,
                          T omega, hipStream_t s, int nsys, int64_t zs, const int* active, int variant, const T* ec,
                          int64_t zc);
-// x1 = S(0, b) and r = b - A x1 in one launch (default penalty: c.ref set;
-// k <= 5, else hipErrorNotSupported).  It recomputes the solves of a two-cell
+// x1 = S(0, b) and r = b - A x1 in one launch (default penalty k <= 5, others
+// k <= 3, else hipErrorNotSupported).  It recomputes the solves of a two-cell
 // halo, which pays only where launches and latency dominate: on levels up to
-// pre2d_max_n(k, element size) cells per direction (0: none).  Measured, fused
-// against two launches: Q3 128^2 float32 7.1 against 9.4 us, 256^2 17.4
-// against 12.6; Q4 128^2 float64 14.3 against 15, 64^2 8.1 against 10; Q6 64^2
-// float64 22.4 against 16.5.
-inline int pre2d_max_n(int k, int elem_size) { return k <= 3 ? 128 : k == 4 ? (elem_size == 4 ? 128 : 64) : k == 5 ? 64 : 0; }
+// pre2d_max_n(k, element size, default penalty) cells per direction (0:
+// none).  Measured, fused against two launches, default penalty: Q3 128^2
+// float32 7.1 against 9.4 us, 256^2 17.4 against 12.6; Q4 128^2 float64 14.3
+// against 15, 64^2 8.1 against 10; Q6 64^2 float64 22.4 against 16.5.  Others,
+// a whole V-cycle without the tail: float64 Q2 64^2 179 against 187, 128^2 218
+// against 230; Q3 64^2 188 against 191, 128^2 235 against 234; float32 Q2
+// 128^2 201 against 212, Q3 128^2 216 against 218.
+inline int pre2d_max_n(int k, int elem_size, bool ref) {
+  if (!ref) return k == 2 ? 128 : k == 3 ? (elem_size == 4 ? 128 : 64) : 0;
+  return k <= 3 ? 128 : k == 4 ? (elem_size == 4 ? 128 : 64) : k == 5 ? 64 : 0;
+}
 template <typename T>
 hipError_t launch_pre2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b, T* x1, T* r, T omega,
                         hipStream_t s);
+// The same for the default penalty (c.ref set).
+template <typename T>
+hipError_t launch_pre2d_ref(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b, T* x1, T* r,
+                            T omega, hipStream_t s);
 template <typename T>
 hipError_t launch_restrict2d(int k, int Nc, const T* rf, T* bc, hipStream_t s, int nsys = 1,
                              int64_t zf = 0, int64_t zc = 0, const int* active = nullptr);

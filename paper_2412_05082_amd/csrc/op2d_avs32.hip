@@ -6,5 +6,7 @@ namespace c0ip {
 template hipError_t launch_avs2d<float>(int, int, const LevelCoef<float>&, const LevelEig<float>&, const float*,
                                         const float*, float*, float, hipStream_t, int, int64_t, const int*, int,
                                         const float*, const float*, int64_t);
+template hipError_t launch_pre2d<float>(int, int, const LevelCoef<float>&, const LevelEig<float>&, const float*,
+                                      float*, float*, float, hipStream_t);
 
 }  // namespace c0ip

@@ -619,6 +619,222 @@ __global__ __launch_bounds__(S::NTH) void avs2d_kernel(const T* __restrict__ x, 
   }
 }
 
+// ------------------------------------------------------------- pre-smoothing
+// The first pre-smoothing step of a V-cycle level and the residual after it,
+// in one launch:  x1 = S(0, b) = omega sum_v R_v^T A~_v^{-1} R_v b  and
+// r = b - A x1.  A workgroup owns TC x TC cells.  The residual on its nodes
+// needs x1 on the tile extended by 2k nodes (two cells), so the workgroup
+// solves every patch covering that region ((TC + 5)^2 patches, from b
+// staged on the tile extended by three cells), sums their corrections into
+// the operator's staged input, and applies the operator's passes.  x1 and r
+// are written on the owned nodes only (owner computes, deterministic).
+// The patches of neighbouring tiles are solved redundantly instead of
+// passing x1 through HBM and a second launch.
+// Up to k = 3: a thread holds its patch's block in registers.
+
+// Fast-diagonalisation solve of one 2D vertex patch in registers (eq.
+// inverse): u = (Q_y (x) Q_x) D^{-1} (Q_y (x) Q_x)^T r for the n x n patch
+// block r (row a = y index, column c = x index), with the generalised
+// eigenbases Q (Q[c' * n + c] = component c' of eigenvector c) and the
+// reciprocal eigenvalue sums D[ap * n + c] = 1 / (lambda_x[c] + lambda_y[ap]).
+// One thread solves one patch: four 1D transforms of n^3 products each, no
+// intermediate trip through LDS.
+// Dinv(ap, c): the reciprocal eigenvalue sum for (y mode ap, x mode c).
+template <typename T, int n, class QX, class QY, class DINV>
+__device__ __forceinline__ void patch_reg(const T* __restrict__ src, int stride, T* __restrict__ dst, QX qx, QY qy,
+                                          DINV dinv) {
+  T t[n][n];
+  // forward along x: t[a][c] = sum_c' Qx[c'][c] r[a][c']
+#pragma unroll
+  for (int a = 0; a < n; ++a) {
+    T in[n];
+#pragma unroll
+    for (int c = 0; c < n; ++c) in[c] = src[a * stride + c];
+#pragma unroll
+    for (int c = 0; c < n; ++c) {
+      T s = 0;
+#pragma unroll
+      for (int cp = 0; cp < n; ++cp) s += qx(cp * n + c) * in[cp];
+      t[a][c] = s;
+    }
+  }
+  // along y per column: forward with Qy^T, scale, back with Qy
+#pragma unroll
+  for (int c = 0; c < n; ++c) {
+    T f[n];
+#pragma unroll
+    for (int ap = 0; ap < n; ++ap) {
+      T s = 0;
+#pragma unroll
+      for (int a = 0; a < n; ++a) s += qy(a * n + ap) * t[a][c];
+      f[ap] = s * dinv(ap, c);
+    }
+#pragma unroll
+    for (int a = 0; a < n; ++a) {
+      T s = 0;
+#pragma unroll
+      for (int ap = 0; ap < n; ++ap) s += qy(a * n + ap) * f[ap];
+      t[a][c] = s;
+    }
+  }
+  // back along x: u[a][c'] = sum_c Qx[c'][c] t[a][c]
+#pragma unroll
+  for (int a = 0; a < n; ++a)
+#pragma unroll
+    for (int cp = 0; cp < n; ++cp) {
+      T s = 0;
+#pragma unroll
+      for (int c = 0; c < n; ++c) s += qx(cp * n + c) * t[a][c];
+      dst[a * n + cp] = s;
+    }
+}
+
+template <typename T, int K_, int TC_, int NTH_>
+struct PreGeo {
+  static constexpr int K = K_, TC = TC_, NTH = NTH_;
+  using G = Geo<K, TC, TC, NTH, 2, 2>;
+  static constexpr int n = 2 * K - 1, NN = n * n;
+  static constexpr int NV = TC + 5;               // patches per direction (vertices cx0-2 .. cx0+TC+2)
+  static constexpr int SB = (TC + 6) * K - 1;     // staged b per direction: nodes (cx0-3)K+1 ..
+  static constexpr int REG_A = SB * SB > G::RY * G::RX ? SB * SB : G::RY * G::RX;   // b, then x1 (operator input)
+  static constexpr int REG_B = NV * NV * NN > G::RY * G::TX ? NV * NV * NN : G::RY * G::TX;  // corrections, then T
+};
+
+template <typename T, class S>
+__global__ __launch_bounds__(S::NTH) void pre2d_kernel(const T* __restrict__ b, T* __restrict__ x1out,
+                                                       T* __restrict__ rout, int N, int n1, const T* __restrict__ tab,
+                                                       int nclass, int left, int right0, int periodic,
+                                                       const T* __restrict__ Qg, const T* __restrict__ lamg, T omega,
+                                                       tile::TileOrder ord) {
+  using G = typename S::G;
+  constexpr int K = S::K, TC = S::TC, n = S::n, NN = S::NN, NV = S::NV, SB = S::SB, NTH = S::NTH;
+  __shared__ T regA[S::REG_A];
+  __shared__ T regB[S::REG_B];
+  __shared__ T sQ[4 * NN];
+  __shared__ T sLam[4 * n];
+  __shared__ T sD[NN];
+  __shared__ T sTab[G::TABMAX];
+  int tbx, tby;
+  if (!tile::tile_of_block(ord, blockIdx.x, tbx, tby)) return;
+  const int cx0 = tbx * TC, cy0 = tby * TC;
+  const int x0 = cx0 * K, y0 = cy0 * K;  // operator tile origin (owned nodes)
+  const int bx0 = (cx0 - 3) * K + 1, by0 = (cy0 - 3) * K + 1;  // staged b origin
+  // b on the staged region (0 outside the interior nodes)
+  {
+    constexpr int NLB = (SB * SB + NTH - 1) / NTH;
+    T v[NLB];
+#pragma unroll
+    for (int q = 0; q < NLB; ++q) {
+      const int e = threadIdx.x + q * NTH;
+      const int rr = e / SB, cc = e - rr * SB;
+      const int gy = by0 + rr, gx = bx0 + cc;
+      v[q] = (e < SB * SB && gx >= 1 && gx <= n1 - 2 && gy >= 1 && gy <= n1 - 2) ? b[(size_t)gy * n1 + gx] : T(0);
+    }
+    stage_eig<T, n, NTH>(Qg, lamg, sQ, sLam, sD);
+#pragma unroll
+    for (int q = 0; q < NLB; ++q) {
+      const int e = threadIdx.x + q * NTH;
+      if (e < SB * SB) regA[e] = v[q];
+    }
+  }
+  stage_tab<T, G>(tab, sTab, nclass,
+                  !(tile_xin<G>(periodic, left, right0, x0) && tile_yin<G>(periodic, left, right0, y0)));
+  __syncthreads();
+  // patch solves for the vertices cx0-2+i, cy0-2+j (i, j < NV) inside the mesh
+  const bool interior = cx0 >= 4 && cx0 + TC <= N - 4 && cy0 >= 4 && cy0 + TC <= N - 4;
+  for (int p = threadIdx.x; p < NV * NV; p += NTH) {
+    const int pyl = p / NV, pxl = p - pyl * NV;
+    const int vx = cx0 - 2 + pxl, vy = cy0 - 2 + pyl;
+    if (vx < 1 || vx > N - 1 || vy < 1 || vy > N - 1) continue;
+    // patch nodes start at (v-1)K+1 = staged origin + (pxl) K
+    const T* src = regA + (pyl * K) * SB + pxl * K;
+    if (interior) {
+      patch_reg<T, n>(src, SB, regB + p * NN, [&](int i) { return Qg[i]; }, [&](int i) { return Qg[i]; },
+                           [&](int ap, int c) { return sD[ap * n + c]; });
+    } else {
+      const int tx = tile::variant(vx, N), ty = tile::variant(vy, N);
+      const T* qx = sQ + tx * NN;
+      const T* qy = sQ + ty * NN;
+      const T* lx = sLam + tx * n;
+      const T* ly = sLam + ty * n;
+      patch_reg<T, n>(src, SB, regB + p * NN, [&](int i) { return qx[i]; }, [&](int i) { return qy[i]; },
+                           [&](int ap, int c) { return T(1) / (lx[c] + ly[ap]); });
+    }
+  }
+  // b on the owned nodes, kept in registers for the residual (regA is overwritten next)
+  T bv[G::NI][G::RW * K];
+#pragma unroll
+  for (int q = 0; q < G::NI; ++q) {
+    const int it = threadIdx.x + q * NTH;
+    const int cg = it / G::TX, l = it - cg * G::TX;
+#pragma unroll
+    for (int w = 0; w < G::RW * K; ++w) {
+      const int rt = cg * G::RW * K + w;
+      // owned node (x0 + l, y0 + rt) = staged b index (3K - 1 + rt, 3K - 1 + l)
+      bv[q][w] = it < G::NIT_Y ? regA[(3 * K - 1 + rt) * SB + 3 * K - 1 + l] : T(0);
+    }
+  }
+  __syncthreads();
+  // x1 = omega * sum of covering corrections on the operator's staged region
+  // (nodes x0 - 2K .. x0 + TC K + 2K), 0 outside the interior nodes
+  T* sX = regA;
+  for (int e = threadIdx.x; e < G::RY * G::RX; e += NTH) {
+    const int rr = e / G::RX, cc = e - rr * G::RX;
+    const int gx = x0 - G::H + cc, gy = y0 - G::H + rr;
+    T a = 0;
+    if (gx >= 1 && gx <= n1 - 2 && gy >= 1 && gy <= n1 - 2) {
+      const int vxa = gx / K, vxb = (gx % K == 0) ? vxa : vxa + 1;
+      const int vya = gy / K, vyb = (gy % K == 0) ? vya : vya + 1;
+      for (int vy = vya; vy <= vyb; ++vy) {
+        if (vy < 1 || vy > N - 1) continue;
+        for (int vx = vxa; vx <= vxb; ++vx) {
+          if (vx < 1 || vx > N - 1) continue;
+          const int p = (vy - cy0 + 2) * NV + (vx - cx0 + 2);
+          const int c = gx - ((vx - 1) * K + 1), r = gy - ((vy - 1) * K + 1);
+          a += regB[p * NN + r * n + c];
+        }
+      }
+      a *= omega;
+    }
+    sX[e] = a;
+  }
+  __syncthreads();
+  T acc[G::NI][G::RW * K];
+  op_tile_any<T, G>(sX, regB, acc, tab, sTab, nclass, left, right0, periodic, x0, y0, n1);
+#pragma unroll
+  for (int q = 0; q < G::NI; ++q) {
+    const int it = threadIdx.x + q * NTH;
+    if (G::NIT_Y % NTH != 0 && it >= G::NIT_Y) break;
+    const int cg = it / G::TX, l = it - cg * G::TX;
+    const int gx = x0 + l;
+#pragma unroll
+    for (int w = 0; w < G::RW * K; ++w) {
+      const int rt = cg * G::RW * K + w, gy = y0 + rt;
+      if (gx < n1 && gy < n1) {
+        const size_t idx = (size_t)gy * n1 + gx;
+        const bool bnd = gx == 0 || gy == 0 || gx == n1 - 1 || gy == n1 - 1;
+        rout[idx] = bnd ? T(0) : bv[q][w] - acc[q][w];
+        x1out[idx] = bnd ? T(0) : sX[(rt + G::H) * G::RX + l + G::H];
+      }
+    }
+  }
+}
+
+template <typename T, int K>
+hipError_t pre2d_tab(int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b, T* x1, T* r, T omega,
+                     hipStream_t s) {
+  using S = PreGeo<T, K, K == 2 ? 8 : 4, 256>;
+  using G = typename S::G;
+  const int n1 = K * N + 1;
+  // tiles over the nodes (the last one holds the boundary node k N), as for the operator
+  const int nt = (n1 + G::TX - 1) / G::TX;
+  auto in = [&](int bt) { return c.periodic && bt * G::TX >= c.left && bt * G::TX + G::TX <= c.right0; };
+  const tile::TileOrder ord = tile::make_order(nt, nt, in, in);
+  pre2d_kernel<T, S><<<tile::order_blocks(ord), S::NTH, 0, s>>>(b, x1, r, N, n1, c.tab, c.nclass, c.left, c.right0,
+                                                                 c.periodic, e.Q, e.lam, omega, ord);
+  return hipGetLastError();
+}
+
 // Tile sizes (owned cells per side) the fused smoother is compiled for;
 // variant 0 is the default, the autotuner may pick any of them per level.
 template <int K> struct FusedTiles;
@@ -673,6 +889,17 @@ hipError_t launch_apply2d(int k, int N, const LevelCoef<T>& c, const Tin* x, con
 #define CALL(K) apply2d_k<Tin, T, K>(N, c, x, b, y, s, nsys, zs, active, xc)
   C0IP_DISPATCH_K(k, CALL)
 #undef CALL
+}
+
+template <typename T>
+hipError_t launch_pre2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b, T* x1, T* r, T omega,
+                        hipStream_t s) {
+  if (c.ref) return launch_pre2d_ref<T>(k, N, c, e, b, x1, r, omega, s);
+  switch (k) {
+    case 2: return pre2d_tab<T, 2>(N, c, e, b, x1, r, omega, s);
+    case 3: return pre2d_tab<T, 3>(N, c, e, b, x1, r, omega, s);
+    default: return hipErrorNotSupported;
+  }
 }
 
 template <typename T>

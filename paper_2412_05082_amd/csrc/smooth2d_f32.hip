@@ -5,7 +5,7 @@ namespace c0ip {
 
 template hipError_t launch_step2d<float>(int, int, const LevelCoef<float>&, const LevelEig<float>&, const float*, const float*,
                                       float*, float, hipStream_t, int, int64_t, const int*, int, const float*, int64_t);
-template hipError_t launch_pre2d<float>(int, int, const LevelCoef<float>&, const LevelEig<float>&, const float*, float*, float*, float,
+template hipError_t launch_pre2d_ref<float>(int, int, const LevelCoef<float>&, const LevelEig<float>&, const float*, float*, float*, float,
                                      hipStream_t);
 template hipError_t launch_patch2d<float>(int, int, const LevelEig<float>&, const float*, const float*, float*, float, hipStream_t,
                                        int, int64_t, const int*);

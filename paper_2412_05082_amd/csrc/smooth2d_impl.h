@@ -455,8 +455,8 @@ hipError_t launch_step2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>&
 }
 
 template <typename T>
-hipError_t launch_pre2d(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b, T* x1, T* r, T omega,
-                        hipStream_t s) {
+hipError_t launch_pre2d_ref(int k, int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* b, T* x1, T* r, T omega,
+                            hipStream_t s) {
 #define CALL(K) pre2d_k<T, K>(N, c, e, b, x1, r, omega, s)
   C0IP_DISPATCH_K(k, CALL)
 #undef CALL
