@@ -181,7 +181,7 @@ hipError_t launch_apply3d_wide(int k, int N, const LevelCoef<T>& c, const Tin* x
 template <typename T>
 hipError_t launch_patch3d(int k, int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega,
                           hipStream_t s);
-// The same for k >= 5, on boxes of cells.
+// The same for k >= 4, on boxes of cells.
 template <typename T>
 hipError_t launch_patch3d_box(int k, int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega,
                               hipStream_t s);

@@ -329,8 +329,8 @@ hipError_t smooth3d_g(int N, const LevelEig<T>& e, const T* r, const T* xin, T* 
   // the patches shared between chunks (Q3 64^3 float32: 129 us with 512, 121
   // with 1024, 134 with 2048).  For k = 4 twice as many (Q4 64^3 float64: 990
   // us with 256, 856 with 512, 903 with 1024).  Small meshes go down to one
-  // cell per chunk: there the march along z sets the time (Q4 16^3 float64:
-  // 54 us at 4 cells, 28 at 1).
+  // cell per chunk: there the march along z sets the time (Q4 16^3 float64,
+  // which boxes take now: 54 us at 4 cells, 28 at 1).
   const int target = (G::K == 2 ? 2048 : 1024) / (sizeof(T) == 4 ? 1 : 2);
   int zcc = N;
   while (zcc > 1 && (int64_t)tx * tx * ((N + zcc - 1) / zcc) < target) zcc = (zcc + 1) / 2;
@@ -350,7 +350,13 @@ hipError_t launch_patch3d(int k, int N, const LevelEig<T>& e, const T* r, const 
   switch (k) {
     case 2: return smooth3d_g<T, typename SmoothCfg<T, 2>::G>(N, e, r, xin, xout, omega, s);
     case 3: return smooth3d_g<T, typename SmoothCfg<T, 3>::G>(N, e, r, xin, xout, omega, s);
-    case 4: return smooth3d_g<T, typename SmoothCfg<T, 4>::G>(N, e, r, xin, xout, omega, s);
+    case 4:
+      // On small meshes the march along z, layer after layer in a few workgroups, sets the time: boxes
+      // (smooth3d_box.hip). S(0, b) in us, march against boxes: float64 2^3 21.4 and 5.8, 8^3 27.1 and 11.6, 16^3 28.0
+      // and 17.7, 32^3 132 and 99, 64^3 500 and 739; float32 2^3 15.8 and 5.8, 16^3 20.0 and 13.9, 32^3 71 and 69,
+      // 64^3 220 and 496.
+      if (N <= 32) return launch_patch3d_box<T>(k, N, e, r, xin, xout, omega, s);
+      return smooth3d_g<T, typename SmoothCfg<T, 4>::G>(N, e, r, xin, xout, omega, s);
     default: return launch_patch3d_box<T>(k, N, e, r, xin, xout, omega, s);
   }
 }

@@ -1,6 +1,7 @@
 // 3D additive vertex-patch solves x_out = x_in + omega sum_v R_v^T A~_v^{-1} R_v r
-// for k >= 5, on boxes of cells (smooth3d.hip holds a patch's lines in
-// registers along a march, which only fits up to k = 4).
+// for k >= 5, and for k = 4 on small meshes, on boxes of cells (smooth3d.hip
+// holds a patch's lines in registers along a march, which only fits up to
+// k = 4, and whose layers follow one another).
 //
 // A workgroup owns TC x TC cells of one layer and solves the patches that
 // touch them.  Sums over patches that overlap along one axis commute with the
@@ -35,6 +36,7 @@ using tile2::scalar;
 using tile::variant;
 
 template <int K> struct PatchBoxThreads;  // a y line per thread, whole waves
+template <> struct PatchBoxThreads<4> { static constexpr int NTH = 192; };
 template <> struct PatchBoxThreads<5> { static constexpr int NTH = 256; };
 template <> struct PatchBoxThreads<6> { static constexpr int NTH = 384; };
 template <> struct PatchBoxThreads<7> { static constexpr int NTH = 512; };
@@ -246,6 +248,7 @@ template <typename T>
 hipError_t launch_patch3d_box(int k, int N, const LevelEig<T>& e, const T* r, const T* xin, T* xout, T omega,
                               hipStream_t s) {
   switch (k) {
+    case 4: return patch3d_box_k<T, 4>(N, e, r, xin, xout, omega, s);
     case 5: return patch3d_box_k<T, 5>(N, e, r, xin, xout, omega, s);
     case 6: return patch3d_box_k<T, 6>(N, e, r, xin, xout, omega, s);
     case 7: return patch3d_box_k<T, 7>(N, e, r, xin, xout, omega, s);
