@@ -27,6 +27,34 @@ __device__ __forceinline__ T mad(T a, T b, T c) {
     return __builtin_fmaf(a, b, c);
 }
 
+// The error of s = a + b (Knuth's two-sum): a + b = s + the result, exactly.
+template <typename T>
+__device__ __forceinline__ T sum_error(T a, T b, T s) {
+  const T c = s - a;
+  return (a - (s - c)) + (b - c);
+}
+
+// 1 / (d + e) for d > 0 and |e| within half a unit in the last place of d,
+// rounded once: Newton's iteration from the hardware reciprocal, with e in its
+// last residual.  With e the error of the eigenvalue sum d, a mode times this
+// is rounded as often as a mode divided by the rounded sum.
+template <typename T>
+__device__ __forceinline__ T recip(T d, T e) {
+  T r;
+  if constexpr (sizeof(T) == 8) {
+    r = __builtin_amdgcn_rcp(d);  // 24 bits or more
+    r = mad(mad(-d, r, T(1)), r, r);
+  } else {
+    r = __builtin_amdgcn_rcpf(d);
+  }
+  return mad(mad(-e, r, mad(-d, r, T(1))), r, r);
+}
+template <typename T>
+__device__ __forceinline__ T recip_sum(T a, T b) {
+  const T d = a + b;
+  return recip(d, sum_error(a, b, d));
+}
+
 // Reference row of factor OP (0 = M, 1 = L, 2 = B) at cell position p.
 template <int K, int OP>
 __device__ __forceinline__ constexpr double ref_coef(int p, int j) {

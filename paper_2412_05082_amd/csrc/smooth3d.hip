@@ -31,6 +31,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "refband.h"
 
 namespace c0ip {
 namespace {
@@ -178,9 +179,12 @@ __device__ __forceinline__ void smooth3d_tile(const T* __restrict__ r, const T* 
           const T lx = sLam[pvariant(vx, N) * n + mx];
 #pragma unroll
           for (int m = 0; m < n; ++m) {
-            const T lxy = lx + sLam[pvariant(vy, N) * n + m];
+            const T ly = sLam[pvariant(vy, N) * n + m], lxy = lx + ly, exy = ref::sum_error(lx, ly, lxy);
 #pragma unroll
-            for (int c = 0; c < n; ++c) rec[m][c] = T(1) / (lxy + sLam[zv * n + c]);
+            for (int c = 0; c < n; ++c) {
+              const T lz = sLam[zv * n + c], d = lxy + lz;
+              rec[m][c] = ref::recip(d, exy + ref::sum_error(lxy, lz, d));
+            }
           }
         }
       }
@@ -244,9 +248,11 @@ __device__ __forceinline__ void smooth3d_tile(const T* __restrict__ r, const T* 
         T a = 0;
 #pragma unroll
         for (int m = 0; m < n; ++m) a += qa[(K - 1 + p) * n + m] * wa[m];
-        if (p > 0) {
+        if (p > 0) {  // a sum of its own: one chain over both patches would round at the size of their sum
+          T b = 0;
 #pragma unroll
-          for (int m = 0; m < n; ++m) a += qb[(p > 0 ? p - 1 : 0) * n + m] * wb[m];
+          for (int m = 0; m < n; ++m) b += qb[(p > 0 ? p - 1 : 0) * n + m] * wb[m];
+          a += b;
         }
         const bool bnd = zp == 0 || gy == 0 || gx + p == 0;
         xout[o + p] = bnd ? T(0) : xv[p] + omega * a;

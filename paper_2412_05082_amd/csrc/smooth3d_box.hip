@@ -158,9 +158,11 @@ __global__ __launch_bounds__(NTH) void patch3d_box_kernel(const T* __restrict__ 
 #pragma unroll
           for (int a = 0; a < n; ++a) {
             const int l = (u - 1) * K + 1 + a;  // owned y node
-            if (l >= 0 && l < TX) {
+            if (l >= 0 && l < TX) {  // a sum of its own per patch: one chain would round at the size of the total
+              T s1 = T(0);
 #pragma unroll
-              for (int c = 0; c < n; ++c) out[l] += Q[a * n + c] * w[c];
+              for (int c = 0; c < n; ++c) s1 += Q[a * n + c] * w[c];
+              out[l] += s1;
             }
           }
         }
@@ -187,9 +189,11 @@ __global__ __launch_bounds__(NTH) void patch3d_box_kernel(const T* __restrict__ 
 #pragma unroll
           for (int a = 0; a < n; ++a) {
             const int l = (s - 1) * K + 1 + a;
-            if (l >= 0 && l < TX) {
+            if (l >= 0 && l < TX) {  // a sum of its own per patch: one chain would round at the size of the total
+              T s1 = T(0);
 #pragma unroll
-              for (int c = 0; c < n; ++c) out[l] += Q[a * n + c] * w[c];
+              for (int c = 0; c < n; ++c) s1 += Q[a * n + c] * w[c];
+              out[l] += s1;
             }
           }
         }

@@ -226,7 +226,7 @@ struct StageEig {
       if ((int)threadIdx.x + u * NTH < 4 * n) sLam[threadIdx.x + u * NTH] = l[u];
 #pragma unroll
     for (int u = 0; u < LD; ++u)
-      if ((int)threadIdx.x + u * NTH < NN) sD[threadIdx.x + u * NTH] = T(1) / (da[u] + db[u]);
+      if ((int)threadIdx.x + u * NTH < NN) sD[threadIdx.x + u * NTH] = ref::recip_sum(da[u], db[u]);
   }
 };
 
@@ -319,7 +319,7 @@ __device__ __forceinline__ void fd_y(const T* __restrict__ sM, T* __restrict__ s
       for (int a = 0; a < n; ++a) in[a] = sM[(py * S::K + a) * S::XP + col];
       tr1<T, n, true>(q, in, w);
 #pragma unroll
-      for (int m = 0; m < n; ++m) w[m] *= INT ? sD[m * n + mx] : T(1) / (lx + sLam[ty * n + m]);
+      for (int m = 0; m < n; ++m) w[m] *= INT ? sD[m * n + mx] : ref::recip_sum(lx, sLam[ty * n + m]);
       if (kBigBasis<T, n>) q = INT ? basis<T, n, true>(q0, 0) : basis<T, n, false>(sQ, ty * S::NN);
       tr1<T, n, false>(q, w, in);
     } else {
@@ -361,9 +361,11 @@ __device__ __forceinline__ void fd_out(const T* __restrict__ sU, T (&out)[S::K],
     T a = qa[(K - 1 + p) * n] * wa[0];
 #pragma unroll
     for (int m = 1; m < n; ++m) a = mad(qa[(K - 1 + p) * n + m], wa[m], a);
-    if (p > 0) {
+    if (p > 0) {  // a sum of its own: one chain over both patches would round at the size of their sum
+      T b = qb[(p > 0 ? p - 1 : 0) * n] * wb[0];
 #pragma unroll
-      for (int m = 0; m < n; ++m) a = mad(qb[(p > 0 ? p - 1 : 0) * n + m], wb[m], a);
+      for (int m = 1; m < n; ++m) b = mad(qb[(p > 0 ? p - 1 : 0) * n + m], wb[m], b);
+      a += b;
     }
     out[p] = a;
   }
