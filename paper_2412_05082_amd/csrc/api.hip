@@ -165,6 +165,7 @@ struct c0ip_problem {
   void mg_level2d(int l, const T* b, T* x);
   // top level of the single-workgroup tail V-cycle in precision T (-1: none)
   int tailLT[2] = {-2, -2};
+  bool tail_ref[2] = {};  // the tail's kernel: compile-time coefficients, or tables
   template <typename T>
   int tail_level();
   template <typename T>
@@ -355,13 +356,16 @@ int c0ip_problem::tail_level() {
   int cap = std::min(L, c0ip::kTailMaxLevels - 1);
   if (mg.tail_levels > 0) cap = std::min(cap, mg.tail_levels - 1);
   int nclass[c0ip::kTailMaxLevels] = {};
-  const bool ref = gamma == (double)(k * (k + 1));  // compile-time coefficients: no table in LDS
+  bool& ref = tail_ref[sizeof(T) == 4 ? 1 : 0];  // compile-time coefficients: no table in LDS
+  ref = gamma == (double)(k * (k + 1));
   auto bytes = [&](int l) { return c0ip::tail_bytes(k, l, ref ? nullptr : nclass, (int)sizeof(T)); };
   for (int l = 0; l <= cap; ++l) {
     nclass[l] = lv[l]->rc.nclass;
     if (bytes(l) > lim) break;
     if (l >= 1) t = l;
   }
+  if (ref && t >= 1 && !c0ip::tail_ref_better(k, t, (int)sizeof(T), mg.pre_steps + mg.post_steps))
+    ref = c0ip::tail_bytes(k, t, nclass, (int)sizeof(T)) > lim;
   if (t >= 1 && (ref ? c0ip::configure_vtail_ref<T>(k, bytes(t)) : c0ip::configure_vtail<T>(k, bytes(t))) != hipSuccess) {
     (void)hipGetLastError();
     t = -1;
@@ -390,7 +394,7 @@ void c0ip_problem::fill_tail(c0ip::TailParams<T>& P) {
   P.pre = mg.pre_steps;
   P.post = mg.post_steps;
   P.coarse_mode = mg.coarse_mode;
-  P.ref = work<T>(LT).coef.ref != nullptr;
+  P.ref = tail_ref[sizeof(T) == 4 ? 1 : 0];
 }
 
 template <typename T>

@@ -201,7 +201,7 @@ struct TailParams {
   const double* Ainv = nullptr;  // level-0 inverse (coarse_mode 0)
   T omega = 0;
   int pre = 1, post = 1, coarse_mode = 0;
-  bool ref = false;  // default penalty: compile-time coefficients (vtail_ref.hip)
+  bool ref = false;  // compile-time coefficients (vtail_ref.hip; default penalty), else tables (vtail.hip)
 };
 // Per-level slot buffers: system s exists on level l iff s < nA[l]; its
 // vectors start at b[l] + s * stride[l] (x likewise).  A system's tail
@@ -218,6 +218,22 @@ struct TailIO {
 // or NULL for the default penalty's kernel).
 int tail_bytes(int k, int LT, const int* nclass, int elem_size);
 int tail_ref_bytes(int k, int LT, int elem_size);
+// Whether the tail with compile-time coefficients is the faster one for the
+// default penalty (levels 0..LT, steps = pre + post).  Not in float64 on the
+// smallest meshes: there a wave's items are few and long, and each of their
+// coefficients takes two scalar moves, where the tables' kernel spreads an
+// output to a lane.  Per smoothing step and level 0.4 to 1.6 us more; what the
+// transfers and the coarse solve save makes up for it in one step each way at
+// degrees 2 and 4.  V-cycle in us, compile-time against tables, 1+1 and 2+2
+// steps: Q3 4^2 18.5 and 17.5, 29.9 and 25.0; 8^2 34.8 and 31.7, 59.3 and
+// 49.9; 16^2 61.2 and 65.2, 109 and 112; Q2 8^2 22.7 and 24.0, 37.1 and 35.7;
+// 16^2 35.7 and 38.3, 60.8 and 60.9; Q4 4^2 23.1 and 24.5, 37.7 and 35.7; 8^2
+// 45 and 59, 78 and 90.
+inline bool tail_ref_better(int k, int LT, int elem_size, int steps) {
+  if (elem_size == 4) return true;
+  if (k == 3) return LT > 2;
+  return steps < 4 || LT > (k == 2 ? 3 : 1);
+}
 // Largest LDS a workgroup may use on the current device.
 int tail_lds_limit();
 // Allow the tail kernel of degree k `bytes` of dynamic LDS (before launch or capture).
