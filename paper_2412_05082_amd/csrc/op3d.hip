@@ -45,12 +45,14 @@
 
 #include "faces3d.h"
 #include "kernels.h"
+#include "rawbuf.h"
 #include "refband.h"
 #include "tiles.h"
 
 namespace c0ip {
 namespace {
 
+using rawbuf::kOff;
 using ref::band_ref;
 using tile::Band;
 
@@ -248,29 +250,6 @@ __device__ __forceinline__ void zscatter(T (&acc)[4 * K + 1][K], const T (&S1)[K
   zterm<T, K, PS, 2>(acc, S2, ref + opaque((2 * nclass + row) * W + H));
 }
 
-// Raw buffer access: an offset at or beyond the buffer's size reads 0 and
-// drops a store, which replaces the per-lane bounds tests of the staging
-// loads, the residual's right-hand side and the output stores.
-constexpr unsigned kOff = 0x80000000u;  // an offset outside every buffer
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-template <typename T>
-__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  if constexpr (sizeof(T) == 8)
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-  else
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-}
-template <typename T>
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned off, T v) {
-  if constexpr (sizeof(T) == 8)
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
-  else
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, 0, 0);
-}
-
 template <typename Tin, typename T, class G, bool RES>
 __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T* __restrict__ b, T* __restrict__ y,
                                              int N, int n1, const T* __restrict__ ref, T hinv, int nclass, int left,
@@ -307,9 +286,9 @@ __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T*
   // planes that contribute to outputs [c0 k, c1 k), without the boundary planes
   const int zA = max((c0 - 2) * K, 1), zB = min((c1 + 1) * K, NK - 1);
   auto load_plane = [&](int z) {  // zeros beyond plane zB
-    const __amdgpu_buffer_rsrc_t r = buf(x + (size_t)z * plane, z <= zB ? pin : 0u);
+    const __amdgpu_buffer_rsrc_t r = rawbuf::make(x + (size_t)z * plane, z <= zB ? pin : 0u);
 #pragma unroll
-    for (int q = 0; q < NL; ++q) v[q] = (T)buf_load<Tin>(r, soff[q]);
+    for (int q = 0; q < NL; ++q) v[q] = (T)rawbuf::load<Tin>(r, soff[q]);
   };
   auto store_plane = [&]() {
 #pragma unroll
@@ -334,9 +313,9 @@ __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T*
 #pragma unroll
       for (int j = 0; j < K; ++j) {
         const int gz = ce * K + j;
-        const __amdgpu_buffer_rsrc_t r = buf(b + (size_t)gz * plane, gz >= 1 && emit_c ? pout : 0u);
+        const __amdgpu_buffer_rsrc_t r = rawbuf::make(b + (size_t)gz * plane, gz >= 1 && emit_c ? pout : 0u);
 #pragma unroll
-        for (int p = 0; p < K; ++p) bq[j][p] = buf_load<T>(r, boff[p]);
+        for (int p = 0; p < K; ++p) bq[j][p] = rawbuf::load<T>(r, boff[p]);
       }
     };
     static_for<0, K>([&](auto psc) {
@@ -363,11 +342,11 @@ __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T*
         // acc = 0 on plane 0; b reads 0 there
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-          const __amdgpu_buffer_rsrc_t r = buf(y + (size_t)(ce * K + j) * plane, pout);
+          const __amdgpu_buffer_rsrc_t r = rawbuf::make(y + (size_t)(ce * K + j) * plane, pout);
 #pragma unroll
           for (int p = 0; p < K; ++p) {
             const T a = boff[p] == kOff ? T(0) : hinv * acc[j][p];
-            buf_store<T>(r, yoff[p], RES ? bq[j][p] - a : a);
+            rawbuf::store<T>(r, yoff[p], RES ? bq[j][p] - a : a);
           }
         }
       }
@@ -448,17 +427,17 @@ hipError_t launch_apply3d(int k, int N, const LevelCoef<T>& c, const Tin* x, con
   // other, sets the time (float64, march against boxes, us: Q2 16^3 11.8 against 6.4, 32^3 12.5 against 12.5,
   // 64^3 30 against 54; Q3 16^3 25.6 against 7.5, 32^3 34 against 24, 64^3 82 against 145; Q4 32^3 91 against 52,
   // 64^3 234 against 368); from degree 5 the march's window does not fit the registers (Q5 32^3 with bands
-  // in loops 1267 us against 184, 8^3 433 against 11).  Boxes address 4k + 1 planes with 31 bits.
+  // in loops 1267 us against 184, 8^3 433 against 11).
   const bool box = k >= 5 || N <= (k == 2 ? 16 : 32);
-  if (box && (4.0 * k + 1) * (k * N + 1) * (k * N + 1) * sizeof(Tin) < 2147483648.0)
-    return launch_apply3d_box<Tin, T>(k, N, c, x, b, y, s);
-  // raw buffer offsets of a plane must stay below 2^31 bytes
-  if ((double)(k * N + 1) * (k * N + 1) * sizeof(T) >= 2147483648.0) return hipErrorInvalidValue;
+  // raw buffer offsets, of 4k + 1 planes of the input in a box and of a plane in the march, must stay below 2^31 bytes
+  const double plane = (double)(k * N + 1) * (k * N + 1);
+  if ((box ? (4.0 * k + 1) * plane * sizeof(Tin) : plane * sizeof(T)) >= 2147483648.0) return hipErrorInvalidValue;
+  if (box) return launch_apply3d_box<Tin, T>(k, N, c, x, b, y, s);
   switch (k) {
     case 2: return apply3d_g<Tin, T, Apply3Cfg<2>::G>(N, c, x, b, y, s);
     case 3: return apply3d_g<Tin, T, Apply3Cfg<3>::G>(N, c, x, b, y, s);
     case 4: return apply3d_g<Tin, T, Apply3Cfg<4>::G>(N, c, x, b, y, s);
-    default: return launch_apply3d_wide<Tin, T>(k, N, c, x, b, y, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

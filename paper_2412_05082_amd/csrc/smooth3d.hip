@@ -30,7 +30,9 @@
 // fixed order (deterministic).
 #include <algorithm>
 
+#include "faces3d.h"
 #include "kernels.h"
+#include "rawbuf.h"
 #include "refband.h"
 
 namespace c0ip {
@@ -40,17 +42,6 @@ namespace {
 // 1 touching the lower boundary, 2 the upper one, 3 both)
 __device__ __forceinline__ int pvariant(int v, int N) { return (v == 1 ? 1 : 0) | (v == N - 1 ? 2 : 0); }
 
-constexpr unsigned kOff = 0x80000000u;  // an offset outside every buffer
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-template <typename T>
-__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  if constexpr (sizeof(T) == 8)
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
-  else
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
-}
 template <int K_, int TC_>
 struct SGeo {
   static constexpr int K = K_, TC = TC_, NTH = 256;
@@ -101,7 +92,7 @@ __device__ __forceinline__ void smooth3d_tile(const T* __restrict__ r, const T* 
     const int gx = (cx0 - 1) * K + 1 + i, gy = (cy0 - 1) * K + 1 + j;
     roff[t] = (e < RS * RS && gx >= 1 && gx <= NK - 1 && gy >= 1 && gy <= NK - 1)
                   ? (unsigned)(gy * n1 + gx) * sizeof(T)
-                  : kOff;
+                  : rawbuf::kOff;
   }
   // this thread's x mode mx of patch column (px, py)
   const int py = tid / G::XW, col = tid - py * G::XW, px = col / n, mx = col - px * n;
@@ -121,9 +112,9 @@ __device__ __forceinline__ void smooth3d_tile(const T* __restrict__ r, const T* 
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       const int zp = vz * K + j;
-      const __amdgpu_buffer_rsrc_t rr = buf(r + (size_t)zp * plane, zp >= 1 && zp <= NK - 1 ? pbytes : 0u);
+      const __amdgpu_buffer_rsrc_t rr = rawbuf::make(r + (size_t)zp * plane, zp >= 1 && zp <= NK - 1 ? pbytes : 0u);
 #pragma unroll
-      for (int t = 0; t < NR; ++t) v[j][t] = buf_load<T>(rr, roff[t]);
+      for (int t = 0; t < NR; ++t) v[j][t] = rawbuf::load<T>(rr, roff[t]);
     }
   };
   load(v0 - 1);
@@ -261,22 +252,6 @@ __device__ __forceinline__ void smooth3d_tile(const T* __restrict__ r, const T* 
   }
 }
 
-// Zeros on the faces x, y, z = kN (boundary nodes no tile owns).
-template <typename T, int NTH>
-__device__ __forceinline__ void zero_faces3(T* __restrict__ y, int n1, int fb) {
-  const int NK = n1 - 1;
-  const int64_t nf = (int64_t)n1 * n1;
-  for (int q = 0; q < 16; ++q) {
-    const int64_t f = ((int64_t)fb * 16 + q) * NTH + threadIdx.x;
-    if (f >= 3 * nf) return;
-    const int face = (int)(f / nf);
-    const int64_t rem = f - face * nf;
-    const int u = (int)(rem % n1), w = (int)(rem / n1);
-    const int gx = face == 0 ? NK : u, gy = face == 0 ? u : (face == 1 ? NK : w), gz = face == 2 ? NK : w;
-    y[((size_t)gz * n1 + gy) * n1 + gx] = T(0);
-  }
-}
-
 // One workgroup per (tile, z chunk), each XCD walking a contiguous band of
 // them (neighbouring tiles share halos in that XCD's L2), then the
 // workgroups that zero the faces.  Bound by vector instructions (Q3 float32:
@@ -292,7 +267,7 @@ __global__ __launch_bounds__(G::NTH, G::K == 3 && sizeof(T) == 4 ? 4 : 1) void s
   const int n1 = G::K * N + 1;
   const int total = tx * tx * nz, L = blockIdx.x;
   if (L >= total) {
-    zero_faces3<T, G::NTH>(xout, n1, L - total);
+    zero_faces<T, G::NTH>(xout, n1, L - total);
     return;
   }
   __shared__ T sR[G::SZR];
@@ -340,9 +315,8 @@ hipError_t smooth3d_g(int N, const LevelEig<T>& e, const T* r, const T* xin, T* 
   const int target = (G::K == 2 ? 2048 : 1024) / (sizeof(T) == 4 ? 1 : 2);
   int zcc = N;
   while (zcc > 1 && (int64_t)tx * tx * ((N + zcc - 1) / zcc) < target) zcc = (zcc + 1) / 2;
-  const int nface = (int)((3 * (int64_t)n1 * n1 + 16 * G::NTH - 1) / (16 * G::NTH));
   const int nz = (N + zcc - 1) / zcc;
-  smooth3d_kernel<T, G><<<tx * tx * nz + nface, G::NTH, 0, s>>>(r, xin, xout, N, e.Q, e.lam, omega, tx, nz, zcc);
+  smooth3d_kernel<T, G><<<tx * tx * nz + face_blocks<G::NTH>(n1), G::NTH, 0, s>>>(r, xin, xout, N, e.Q, e.lam, omega, tx, nz, zcc);
   return hipGetLastError();
 }
 

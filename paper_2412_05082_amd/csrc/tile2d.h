@@ -20,6 +20,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "rawbuf.h"
 #include "refband.h"
 #include "tiles.h"
 
@@ -59,32 +60,20 @@ struct Op {
 // load outside them reads 0 and a store is dropped, which replaces the bounds
 // tests (kOff: an offset outside every buffer).  Offsets are bytes from the
 // start of row rlo; rows below it give offsets that wrap to huge values.
-constexpr unsigned kOff = 0x80000000u;
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+using rawbuf::kOff;
 template <typename T>
 struct Rows {
   __amdgpu_buffer_rsrc_t r;
   int rlo, n1;
   __device__ __forceinline__ Rows(const T* p, int n1_, int rlo_, int rhi) : rlo(rlo_), n1(n1_) {
     const int cnt = rhi - rlo_ + 1;
-    r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p) + (size_t)rlo_ * n1_, (short)0,
-                                          cnt > 0 ? cnt * n1_ * (int)sizeof(T) : 0, 0x00020000);
+    r = rawbuf::make(p + (size_t)rlo_ * n1_, cnt > 0 ? cnt * n1_ * (int)sizeof(T) : 0);
   }
   __device__ __forceinline__ unsigned off(int row, int col) const {
     return (unsigned)(((row - rlo) * n1 + col) * (int)sizeof(T));
   }
-  __device__ __forceinline__ T load(unsigned o) const {
-    if constexpr (sizeof(T) == 8)
-      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)o, 0, 0));
-    else
-      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)o, 0, 0));
-  }
-  __device__ __forceinline__ void store(unsigned o, T v) const {
-    if constexpr (sizeof(T) == 8)
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)o, 0, 0);
-    else
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)o, 0, 0);
-  }
+  __device__ __forceinline__ T load(unsigned o) const { return rawbuf::load<T>(r, o); }
+  __device__ __forceinline__ void store(unsigned o, T v) const { rawbuf::store<T>(r, o, v); }
 };
 
 // Stage a W x HT window (first node (gx0, gy0)) of x in LDS rows of stride
