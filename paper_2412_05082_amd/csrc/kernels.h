@@ -129,7 +129,7 @@ template <typename T>
 hipError_t launch_mvs2d_colour_ref(int k, int N, int colour, const LevelCoef<T>& c, const T* Q, const T* lam,
                                    const T* Aex, const T* b, const T* r, T* x, T omega, hipStream_t s);
 // One fused smoothing step S(x, b) (residual in LDS; x_out must not alias x).
-// variant: tile-size variant (0 = default; below avs2d_variants).  With ec:
+// variant: tile-size variant (0 = default; below avs2d_variants(k)).  With ec:
 // the step starts from x + P ec instead (ec: coarse vector of the level
 // below, zc apart between systems; ptab: the embedding table).
 template <typename T>

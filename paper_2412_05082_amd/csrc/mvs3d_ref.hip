@@ -34,9 +34,10 @@ namespace {
 using ref::band_ref;
 using tile::variant;
 
-// P patches on NTH threads: an item of each part of the x pass and of the y pass per thread, and rows of the colour
-// (N / 4 patches) that P divides well.  Q2 128^3 float32, us a step: P = 6 1100, 4 1265, 8 1233 (384 threads), 3 1393;
-// float64 P = 4 2130, 6 2650; Q3 64^3 float32 P = 2 593, 1 663, 3 750; Q4 32^3 P = 1 316, 2 322.
+// P patches on NTH threads, by a sweep: about an item of each part of the x pass and of the y pass per thread. Where P
+// does not divide a row of the colour (N / 4 patches) its last workgroup is partly idle. Q2 128^3 float32, us a step:
+// P = 6 1100, 4 1265, 8 1233 (384 threads), 3 1393; float64 P = 4 2130, 6 2650; Q3 64^3 float32 P = 2 593, 1 663,
+// 3 750; Q4 32^3 P = 1 316, 2 322.
 template <int K, int ES> struct Shape3;  // degree, bytes per value
 template <int ES> struct Shape3<2, ES> { static constexpr int P = ES == 4 ? 6 : 4, NTH = 256; };
 template <int ES> struct Shape3<3, ES> { static constexpr int P = 2, NTH = 256; };

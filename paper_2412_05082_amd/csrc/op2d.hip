@@ -3,6 +3,7 @@
 
 namespace c0ip {
 
+// Variants that a caller may set: the tile sizes of the tables' kernel.
 int avs2d_variants(int k) {
   switch (k) {
     case 2: return FusedTiles<2>::n;

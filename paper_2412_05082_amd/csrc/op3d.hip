@@ -365,8 +365,10 @@ __device__ __forceinline__ void apply3d_tile(const Tin* __restrict__ x, const T*
 // One workgroup per (tile, z chunk), each XCD walking a contiguous band of
 // them (x fastest, then y: neighbouring tiles share halos in that XCD's L2),
 // then the workgroups that zero the faces.
-// The register bound holds Q3 float64 at 3 waves per SIMD (residual form at
-// 128^3: 592 us at 2 waves, 509 at 3).
+// The register bound holds the residual form of Q3 float64 at 3 waves per SIMD
+// (170 registers and 2 waves without it: S(x, b) at 128^3 1325 us against
+// 1187).  The other degrees and types are left to the compiler: 54 to 100
+// registers, or for Q4 float64 all 256, where a bound would spill the window.
 template <typename Tin, typename T, class G, bool RES>
 __global__ __launch_bounds__(G::NTH, G::K == 3 && sizeof(T) == 8 ? 3 : 1) void apply3d_kernel(
     const Tin* __restrict__ x, const T* __restrict__ b, T* __restrict__ y, int N, int n1, const T* __restrict__ ref,
@@ -401,10 +403,11 @@ hipError_t apply3d_g(int N, const LevelCoef<T>& c, const Tin* x, const T* b, T* 
   // z chunks: 1024 workgroups (what the chip holds at 3 waves per SIMD), down
   // to one cell per chunk: a chunk recomputes 3k + 1 halo planes, but below
   // 1024 workgroups the march along z sets the time (3D Q3 32^3 float64, which
-  // boxes take now: 63 us at 8 cells per chunk, 43 at 4, 33 at 1).  Twice as many for Q3 float64
-  // from 128^3: there the halos come from HBM once the workgroups of a plane
-  // have drifted apart along a long march (128^3: 476 us against 420; 256^3:
-  // 4239 against 3222; float32 and the other degrees are slower by up to 15 %).
+  // boxes take now: 63 us at 8 cells per chunk, 43 at 4, 33 at 1).  Twice as
+  // many for Q3 float64 from 128^3: there the halos come from HBM once the workgroups of a plane have drifted apart
+  // (A x in us, 1024 against 2048: 128^3 453 and 440, 256^3 3993 and 3164). For the others the halo planes cost more
+  // up to 128^3 (Q3 64^3 float64 85 and 121; 128^3 Q2 float64 92 and 105, Q3 float32 212 and 242, Q4 float64 1415 and
+  // 1595), and 256^3 would gain little (Q2 float64 678 and 663, Q3 float32 1781 and 1698).
   const int target = G::K == 3 && sizeof(T) == 8 && N >= 128 ? 2048 : 1024;
   int zcc = N;
   while (zcc > 1 && (int64_t)tx * ty * ((N + zcc - 1) / zcc) < target) zcc = (zcc + 1) / 2;

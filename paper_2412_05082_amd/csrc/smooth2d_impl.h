@@ -379,6 +379,10 @@ hipError_t patch2d_g(int N, const LevelEig<T>& e, const T* r, const T* xin, T* x
 // tiles costs most.  Small: below that one workgroup's latency sets the time.
 // k <= 4 takes large tiles (12 cells; 6 in Q3 float64, where LDS limits the
 // workgroups per compute unit); from k = 5 on the LDS of one tile does.
+// S(x, b) at 256^2 in us, large against small tile: float32 Q3 9.7 and 12.5,
+// Q4 18.5 and 20.4, Q5 27 and 51, Q6 53 and 94, Q7 74 and 234; float64 Q3 15.6
+// and 20.0, Q4 30 and 38, Q5 62 and 119, Q7 247 and 437, but Q6 184 and 171
+// (the bases overflow the registers of the large tile).
 template <int TC_, int NTH_, int CW_>
 struct Tile {
   static constexpr int TC = TC_, NTH = NTH_, CW = CW_;
@@ -412,7 +416,8 @@ inline bool fills(int N, int TC, int nsys) {
   return t * t * nsys >= 256;
 }
 
-// variant: 0 = by the mesh, 1 = the small tile, 2 = the large one.
+// variant: 0 = by the mesh, 1 = the small tile, 2 = the large one (which c0ip_set_variant and the autotuner offer up to
+// k = 3, where the tables' kernel has three tiles; for this kernel the autotuner times one of the two tiles twice).
 template <typename T, int K>
 hipError_t step2d_k(int N, const LevelCoef<T>& c, const LevelEig<T>& e, const T* x, const T* b, T* xout, T omega,
                     hipStream_t s, int nsys, int64_t zs, const int* active, int variant, const T* ec, int64_t zc) {

@@ -255,10 +255,13 @@ __device__ __forceinline__ void smooth3d_tile(const T* __restrict__ r, const T* 
 // One workgroup per (tile, z chunk), each XCD walking a contiguous band of
 // them (neighbouring tiles share halos in that XCD's L2), then the
 // workgroups that zero the faces.  Bound by vector instructions (Q3 float32:
-// they issue in 78 % of the time).  3D Q3 128^3, this kernel alone: float32
-// 891 -> 400 us with the register windows in place of six passes over every
-// patch's block in LDS, float64 1826 -> 780 us.  The register bound holds Q3
-// float32 at 4 waves per SIMD (3 waves: 8 % slower).
+// they take 84 % of the SIMDs' issue slots).  3D Q3 128^3, this kernel alone:
+// float32 891 -> 400 us with the register windows in place of six passes over
+// every patch's block in LDS, float64 1826 -> 780 us.  The register bound
+// holds Q3 float32 at 4 waves per SIMD (136 registers and 3 waves without it:
+// S(x, b) 128^3 692 us against 630).  The other degrees and types are left to
+// the compiler: Q2 stays at 4 waves and more, Q3 float64 and Q4 take 237 to all
+// 256 registers, and a tighter bound would spill their windows.
 template <typename T, class G>
 __global__ __launch_bounds__(G::NTH, G::K == 3 && sizeof(T) == 4 ? 4 : 1) void smooth3d_kernel(const T* __restrict__ r, const T* __restrict__ xin,
                                                           T* __restrict__ xout, int N, const T* __restrict__ Qg,
