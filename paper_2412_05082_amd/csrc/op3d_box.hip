@@ -11,7 +11,7 @@
 // accumulators: the march holds (4k+1) k of them per thread, which only fits
 // up to k = 4.  Small meshes are bound by the latency of the three phases (Q5
 // 4^3 float64 429 -> 11 us, Q3 16^3 57 -> 7.5), large ones by instruction
-// issue (at Q5 32^3 float64 vector instructions take 43 % of the SIMDs' slots,
+// issue (at Q5 32^3 float64 vector instructions take 40 % of the SIMDs' slots,
 // with nearly as many scalar ones beside them: 1267 -> 184 us, Q7 32^3 5084 ->
 // 630), most of it for the columns that neighbouring boxes recompute.
 #include <type_traits>

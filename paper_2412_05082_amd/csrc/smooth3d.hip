@@ -255,7 +255,7 @@ __device__ __forceinline__ void smooth3d_tile(const T* __restrict__ r, const T* 
 // One workgroup per (tile, z chunk), each XCD walking a contiguous band of
 // them (neighbouring tiles share halos in that XCD's L2), then the
 // workgroups that zero the faces.  Bound by vector instructions (Q3 float32:
-// they take 84 % of the SIMDs' issue slots).  3D Q3 128^3, this kernel alone:
+// they take 74 % of the SIMDs' issue slots).  3D Q3 128^3, this kernel alone:
 // float32 891 -> 400 us with the register windows in place of six passes over
 // every patch's block in LDS, float64 1826 -> 780 us.  The register bound
 // holds Q3 float32 at 4 waves per SIMD (136 registers and 3 waves without it:

@@ -178,7 +178,7 @@ struct Tail {
         for (int a = 0; a < n; ++a) in[a] = s[((v - 1) * K + a) * XP + col];
         tile2::tr1<T, n, true>(q, in, w);
 #pragma unroll
-        for (int m = 0; m < n; ++m) w[m] *= ref::recip_sum(lx, lam[ty * n + m]);
+        for (int m = 0; m < n; ++m) w[m] /= lx + lam[ty * n + m];
         tile2::tr1<T, n, false>(q, w, in);
 #pragma unroll
         for (int a = 0; a < n; ++a) sU[((v - 1) * n + a) * XP + col] = in[a];
